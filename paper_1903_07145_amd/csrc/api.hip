@@ -60,6 +60,7 @@ struct ipt_scene_s {
     SceneDev dev{};
     float4* d_nodes = nullptr;
     float4* d_tris = nullptr;
+    float4* d_axis = nullptr;    // the triangles by axis (ray streams)
     float4* d_nrm = nullptr;
     int4* d_lights = nullptr;
     int* d_segemit = nullptr;
@@ -112,20 +113,24 @@ static void prof_clear_events(ipt_scene_s* s) {
     }
 }
 
-// Launch a path kernel, bracketed by events when profiling is on.
-static hipError_t timed_launch(ipt_scene_s* s, int mode, PathArgs& a, int grid, size_t lds, hipStream_t st) {
+// Launch the kernels of a path pass, bracketed by events when profiling is on.
+template <class F>
+static hipError_t timed_pass(ipt_scene_s* s, int mode, PathArgs& a, hipStream_t st, F launch) {
     a.count_stats = s->prof ? 1 : 0;
-    if (!s->prof) return launch_paths(mode, a, grid, lds, st);
+    if (!s->prof) return launch();
     hipEvent_t e0, e1;
     hipError_t e = hipEventCreate(&e0);
     if (e != hipSuccess) return e;
     e = hipEventCreate(&e1);
     if (e != hipSuccess) return e;
     hipEventRecord(e0, st);
-    e = launch_paths(mode, a, grid, lds, st);
+    e = launch();
     hipEventRecord(e1, st);
     s->ev[mode].push_back({e0, e1});
     return e;
+}
+static hipError_t timed_launch(ipt_scene_s* s, int mode, PathArgs& a, int grid, size_t lds, hipStream_t st) {
+    return timed_pass(s, mode, a, st, [&] { return launch_paths(mode, a, grid, lds, st); });
 }
 
 // ---------------------------------------------------------------------------
@@ -136,6 +141,7 @@ extern "C" ipt_status ipt_scene_free(ipt_scene_t s) {
     prof_clear_events(s);
     hipFree(s->d_nodes);
     hipFree(s->d_tris);
+    hipFree(s->d_axis);
     hipFree(s->d_nrm);
     hipFree(s->d_lights);
     hipFree(s->d_segemit);
@@ -316,12 +322,14 @@ extern "C" ipt_status ipt_scene_build_ex(const float* verts, int64_t nv, const f
 
     // leaf-ordered triangle records, shading normals, inverse permutation, light table
     if (e == hipSuccess) e = hipMalloc((void**)&s->d_tris, sizeof(float4) * 3 * nt);
+    if (e == hipSuccess) e = hipMalloc((void**)&s->d_axis, sizeof(float4) * 3 * nt);
     if (e == hipSuccess && normals) e = hipMalloc((void**)&s->d_nrm, sizeof(float4) * 3 * nt);
     if (e == hipSuccess) e = hipMalloc((void**)&s->d_pos_of, sizeof(int) * std::max<int64_t>(nt, 4));
     if (e == hipSuccess) e = up((void**)&s->d_lights, lights.data(), lights.size() * sizeof(int4), false);
     if (e == hipSuccess) e = up((void**)&s->d_segemit, seg_emitter.data(), seg_emitter.size() * sizeof(int), false);
     if (e == hipSuccess)
-        e = launch_scene_layout(d_verts, d_tris, d_seg, d_lot, d_vnrm, d_order, nt, s->d_tris, s->d_nrm, s->d_pos_of,
+        e = launch_scene_layout(d_verts, d_tris, d_seg, d_lot, d_vnrm, d_order, nt, s->d_tris, s->d_axis, s->d_nrm,
+                                s->d_pos_of,
                                 s->d_lights, (int)lights.size(), st);
     if (e == hipSuccess) e = hipMalloc((void**)&s->d_err, sizeof(Counters));
     if (e == hipSuccess) e = hipMemsetAsync(s->d_err, 0, sizeof(Counters), st);
@@ -352,6 +360,7 @@ extern "C" ipt_status ipt_scene_build_ex(const float* verts, int64_t nv, const f
     for (int a = 0; a < 3; ++a) { s->bb_lo[a] = lo[a]; s->bb_hi[a] = hi[a]; }
     s->dev.nodes = s->d_nodes;
     s->dev.tris = s->d_tris;
+    s->dev.tri_axis = s->d_axis;
     s->dev.nrm = s->d_nrm;
     s->dev.lights = s->d_lights;
     s->dev.seg_emitter = s->d_segemit;
@@ -504,6 +513,34 @@ static size_t plan_min(const Plan& pl, int64_t npix) {
 }
 static size_t plan_full(const Plan& pl, int64_t npix) { return pl.end_fixed + 4 * 256 + (size_t)npix * pl.ck_per_pixel; }
 
+// Path streams or the per-lane state machine?  Returns the pixels per batch of
+// streams that fit into `bytes` of scratch, 0 for the state machine.  Streams
+// are faster at every size; the state machine runs what they do not provide
+// (path hashes, vertex records, the proposal network at every vertex), and
+// passes whose scratch holds neither all paths nor a batch of 2^20, where the
+// batches' launches would cost more than they save.  Few large batches: the
+// apartment's step of 39 M paths takes 108 / 102 / 100 / 97 ms in batches of at
+// most 4 / 8 / 16 / 40 M.
+constexpr int64_t kStreamMaxPaths = 40 << 20;
+static int64_t stream_batch(const ipt_scene_s* s, const ipt_render_opts* o, int64_t npix, size_t bytes) {
+    const int64_t npaths = npix * o->spp;
+    const int gk = guide_kind(o);
+    if (gk == 1 || gk == 2 || o->debug_path_hash || o->debug_vertices) return 0;
+    const size_t fixed = stream_fixed_bytes(s->num_cu);
+    if (bytes <= fixed) return 0;
+    const int64_t room = std::min<int64_t>((int64_t)((bytes - fixed) / kStreamPathBytes), kStreamMaxPaths);
+    if (room < std::min<int64_t>(npaths, 1 << 20)) return 0;
+    const int64_t pixels = std::min<int64_t>(npix, room / o->spp);
+    if (pixels < 1) return 0;
+    const int64_t batches = (npix + pixels - 1) / pixels;
+    return (npix + batches - 1) / batches;
+}
+// Scratch that the largest batches need.
+static size_t stream_full(const ipt_scene_s* s, const ipt_render_opts* o, int64_t npix) {
+    return stream_fixed_bytes(s->num_cu) +
+           kStreamPathBytes * (size_t)std::min<int64_t>(npix * o->spp, kStreamMaxPaths);
+}
+
 extern "C" ipt_status ipt_workspace_query(ipt_scene_t s, const ipt_cameras* cams, const ipt_render_opts* o,
                                           size_t* min_bytes, size_t* full_bytes) {
     if (!s || !min_bytes || !full_bytes) return fail(IPT_ERR_INVALID_ARG, "NULL argument");
@@ -513,7 +550,7 @@ extern "C" ipt_status ipt_workspace_query(ipt_scene_t s, const ipt_cameras* cams
     Plan pl;
     make_plan(s, o, npix, true, pl);
     *min_bytes = plan_min(pl, npix);
-    *full_bytes = plan_full(pl, npix);
+    *full_bytes = plan_full(pl, npix) + stream_full(s, o, npix) + 512;
     return IPT_OK;
 }
 
@@ -562,7 +599,7 @@ static PathArgs base_args(const ipt_scene_s* s, const ipt_cameras* cams, const f
 
 static ipt_status do_render(ipt_scene_t s, const ipt_cameras* cams, const float* params, const float* sp,
                             const ipt_render_opts* o, int64_t npix, float* image, unsigned char* ws,
-                            const Plan& pl, hipStream_t st, bool allow_profile = true) {
+                            size_t ws_bytes, const Plan& pl, hipStream_t st, bool allow_profile = true) {
     PathArgs a = base_args(s, cams, params, sp, o, ws, pl);
     a.image = image;
     a.pix_begin = 0;
@@ -573,7 +610,11 @@ static ipt_status do_render(ipt_scene_t s, const ipt_cameras* cams, const float*
     HIP_OK(launch_zero_u32(a.work, 1, st));
     size_t lds = path_lds_bytes(kColor, a.P, a.frozen, s->S, s->nlt, a.guide_kind, a.params_global);
     int grid = (int)std::min<int64_t>(pl.grid, (npix * a.nchunk + kBlock - 1) / kBlock);
-    if (allow_profile) {
+    const int64_t batch = stream_batch(s, o, npix, ws_bytes > pl.end_fixed ? ws_bytes - pl.end_fixed : 0);
+    if (batch > 0) {
+        const StreamArgs t = stream_layout(ws + pl.end_fixed, s->num_cu, batch * o->spp);
+        HIP_OK(timed_pass(s, kColor, a, st, [&] { return launch_stream_pass(kColor, a, t, batch, s->num_cu, st); }));
+    } else if (allow_profile) {
         HIP_OK(timed_launch(s, kColor, a, std::max(1, grid), lds, st));
     } else {
         a.count_stats = 0;
@@ -589,9 +630,19 @@ static ipt_status do_grad(ipt_scene_t s, const ipt_cameras* cams, const float* p
     PathArgs a = base_args(s, cams, params, sp, o, ws, pl);
     a.w = w;
     split_samples(npix, o->spp, pl.grid, a.spc, a.nchunk);
-    // chunk size from the space left for checkpoints
-    size_t avail = ws_bytes > pl.end_fixed + 4 * 256 ? ws_bytes - pl.end_fixed - 4 * 256 : 0;
-    int64_t chunk = (int64_t)(avail / pl.ck_per_pixel);
+    // pixels per chunk from the space for checkpoints; streams take at most a
+    // quarter of the space where the checkpoints do not leave them more
+    const size_t avail = ws_bytes > pl.end_fixed + 4 * 256 ? ws_bytes - pl.end_fixed - 4 * 256 : 0;
+    const size_t all_ck = (size_t)npix * pl.ck_per_pixel;
+    int64_t batch = stream_batch(s, o, npix, std::max(avail / 4, avail - std::min(avail, all_ck)));
+    size_t stream_bytes = batch > 0 ? 256 + al256(stream_fixed_bytes(s->num_cu) + kStreamPathBytes * (size_t)(batch * o->spp)) : 0;
+    int64_t chunk = (int64_t)((avail - stream_bytes) / pl.ck_per_pixel);
+    if (batch > 0 && chunk < std::min<int64_t>(npix, kBlock)) {
+        batch = 0;
+        stream_bytes = 0;
+        chunk = (int64_t)(avail / pl.ck_per_pixel);
+    }
+    unsigned char* stream_ws = ws + ((ws_bytes - stream_bytes) & ~size_t(255));
     if (chunk < npix) chunk = (chunk / kBlock) * kBlock;
     chunk = std::min<int64_t>(chunk, npix);
     if (chunk < 1) return fail(IPT_ERR_WORKSPACE_TOO_SMALL, "workspace too small for one gradient chunk");
@@ -616,7 +667,12 @@ static ipt_status do_grad(ipt_scene_t s, const ipt_cameras* cams, const float* p
         a.pix_count = std::min<int64_t>(chunk, npix - b);
         int grid = (int)std::max<int64_t>(1, std::min<int64_t>(pl.grid, (a.pix_count * a.nchunk + kBlock - 1) / kBlock));
         HIP_OK(launch_zero_u32(a.work, 1, st));
-        HIP_OK(timed_launch(s, kGradFwd, a, grid, lds_f, st));
+        if (batch > 0) {
+            const StreamArgs t = stream_layout(stream_ws, s->num_cu, batch * o->spp);
+            HIP_OK(timed_pass(s, kGradFwd, a, st, [&] { return launch_stream_pass(kGradFwd, a, t, batch, s->num_cu, st); }));
+        } else {
+            HIP_OK(timed_launch(s, kGradFwd, a, grid, lds_f, st));
+        }
         if (a.guided) HIP_OK(launch_guide_records(a, st));
         // the replay pulls tiles, so it runs on as many blocks as are resident
         int grid_r = std::min(grid, s->num_cu * std::max(1, path_blocks_per_cu(kReplay, lds_r, 0, a.params_global, a.mat)));
@@ -639,8 +695,8 @@ extern "C" ipt_status ipt_render(ipt_scene_t s, const ipt_cameras* cams, const f
     make_plan(s, o, npix, false, pl);
     if (!workspace || workspace_bytes < pl.end_fixed)
         return fail(IPT_ERR_WORKSPACE_TOO_SMALL, "workspace needs %zu bytes", pl.end_fixed);
-    return do_render(s, cams, params, sampling_params, o, npix, image, (unsigned char*)workspace, pl,
-                     (hipStream_t)hip_stream);
+    return do_render(s, cams, params, sampling_params, o, npix, image, (unsigned char*)workspace,
+                     workspace_bytes, pl, (hipStream_t)hip_stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -710,7 +766,8 @@ extern "C" ipt_status ipt_render_static(ipt_scene_t s, const ipt_cameras* cams, 
     unsigned char* ws = nullptr;
     stt = scratch_for_device(dev, &ws);
     if (stt != IPT_OK) return stt;
-    return do_render(s, cams, params, sampling_params, o, npix, image, ws, pl, (hipStream_t)hip_stream, false);
+    return do_render(s, cams, params, sampling_params, o, npix, image, ws, need, pl, (hipStream_t)hip_stream,
+                     false);
 }
 
 extern "C" ipt_status ipt_render_grad(ipt_scene_t s, const ipt_cameras* cams, const float* params,
@@ -749,7 +806,7 @@ extern "C" ipt_status ipt_loss_grad(ipt_scene_t s, const ipt_cameras* cams, cons
     hipStream_t st = (hipStream_t)hip_stream;
     float* img = image_A ? image_A : (float*)(ws + pl.off_img);
     float* w = (float*)(ws + pl.off_w);
-    stt = do_render(s, cams, params, nullptr, co, npa, img, ws, pl, st);
+    stt = do_render(s, cams, params, nullptr, co, npa, img, ws, workspace_bytes, pl, st);
     if (stt != IPT_OK) return stt;
     HIP_OK(launch_loss_adjoint(img, target, 3 * npa, loss_kind, w, (float*)(ws + pl.off_loss), 1024, loss, st));
     return do_grad(s, cams, params, nullptr, go, npb, w, grad, ws, workspace_bytes, pl, st);

@@ -20,10 +20,11 @@ struct GpuBvh {
 std::string build_bvh_gpu(const float* d_verts, const int* d_tris, int64_t nt, hipStream_t st, GpuBvh& out);
 
 // Leaf-ordered triangle records (v0, orig id) (v1, segment) (v2, light index),
+// the same triangles by axis (taxis: x, y, z of the three vertices, id),
 // shading normals (when d_normals != NULL) and the inverse permutation
 // pos_of [nt]; then lights[j].x = pos_of[lights[j].w].
 hipError_t launch_scene_layout(const float* d_verts, const int* d_tris, const int* d_seg, const int* d_light_of_tri,
                                const float* d_normals, const int* d_leaf_order, int64_t nt, float4* trec,
-                               float4* nrec, int* pos_of, int4* lights, int nlt, hipStream_t st);
+                               float4* taxis, float4* nrec, int* pos_of, int4* lights, int nlt, hipStream_t st);
 
 }  // namespace ipt

@@ -675,20 +675,24 @@ __global__ __launch_bounds__(kTB) void k_stats(const GNode* nodes, int N, double
 // ---------------------------------------------------------------------------
 __global__ void k_tri_records(const float* __restrict__ v, const int* __restrict__ tri, const int* __restrict__ seg,
                               const int* __restrict__ light_of_tri, const float* __restrict__ nrm,
-                              const int* __restrict__ order, int64_t nt, float4* trec, float4* nrec, int* pos_of) {
+                              const int* __restrict__ order, int64_t nt, float4* trec, float4* taxis, float4* nrec,
+                              int* pos_of) {
     int64_t p = (int64_t)blockIdx.x * kTB + threadIdx.x;
     if (p >= nt) return;
     int t = order[p];
+    float c[3][3];
     for (int j = 0; j < 3; ++j) {
         int vi = tri[3 * (int64_t)t + j];
         const float* x = v + 3 * (int64_t)vi;
         int tag = j == 0 ? t : (j == 1 ? seg[t] : light_of_tri[t]);
         trec[3 * p + j] = make_float4(x[0], x[1], x[2], __int_as_float(tag));
+        for (int a = 0; a < 3; ++a) c[a][j] = x[a];
         if (nrm) {
             const float* q = nrm + 3 * (int64_t)vi;
             nrec[3 * p + j] = make_float4(q[0], q[1], q[2], 0.0f);
         }
     }
+    for (int a = 0; a < 3; ++a) taxis[3 * p + a] = make_float4(c[a][0], c[a][1], c[a][2], __int_as_float(t));
     pos_of[t] = (int)p;
 }
 
@@ -927,9 +931,9 @@ std::string build_bvh_gpu(const float* d_verts, const int* d_tris, int64_t nt, h
 
 hipError_t launch_scene_layout(const float* d_verts, const int* d_tris, const int* d_seg, const int* d_light_of_tri,
                                const float* d_normals, const int* d_leaf_order, int64_t nt, float4* trec,
-                               float4* nrec, int* pos_of, int4* lights, int nlt, hipStream_t st) {
+                               float4* taxis, float4* nrec, int* pos_of, int4* lights, int nlt, hipStream_t st) {
     hipLaunchKernelGGL(k_tri_records, dim3(blocks_for(nt)), dim3(kTB), 0, st, d_verts, d_tris, d_seg, d_light_of_tri,
-                       d_normals, d_leaf_order, nt, trec, nrec, pos_of);
+                       d_normals, d_leaf_order, nt, trec, taxis, nrec, pos_of);
     if (nlt > 0) hipLaunchKernelGGL(k_light_pos, dim3(blocks_for(nlt)), dim3(kTB), 0, st, lights, nlt, pos_of);
     return hipGetLastError();
 }

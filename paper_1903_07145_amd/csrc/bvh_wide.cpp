@@ -13,7 +13,8 @@
 // power-of-two cell size per axis.  Layout per node, 16 floats = 64 B:
 //   row 0: origin x, y, z (float); biased exponents e_x, e_y, e_z (bytes 0-2)
 //   row 1: x lo, x hi, y lo, y hi of the four children (one byte per child)
-//   row 2: z lo, z hi, 0, 0
+//   row 2: z lo, z hi; the cell sizes 2^(e + 24) of x and y (the upper 16 bits
+//          of a float each, y's in the low half) and of z (float)
 //   row 3: the four child references (as the float layout)
 // A plane decodes to origin + q 2^e.  Every decoded box contains its child's
 // float box widened by delta = 2^-20 of the node's largest extent on every
@@ -188,7 +189,12 @@ void quantize_wide(std::vector<float>& wide) {
         float* d = &q[16 * id];
         d[0] = org[0]; d[1] = org[1]; d[2] = org[2]; d[3] = bits_f((int)ew);
         d[4] = pack(ql[0]); d[5] = pack(qh[0]); d[6] = pack(ql[1]); d[7] = pack(qh[1]);
-        d[8] = pack(ql[2]); d[9] = pack(qh[2]); d[10] = 0.0f; d[11] = 0.0f;
+        d[8] = pack(ql[2]); d[9] = pack(qh[2]); 
+        // the traversal's cell sizes, with the 2^24 that turns a byte read as an
+        // fp16 subnormal back into an integer
+        auto size = [&](int a) { return (uint32_t)bits_i((float)std::ldexp(1.0, ex[a] + 24)); };
+        d[10] = bits_f((int)(size(0) | size(1) >> 16));
+        d[11] = bits_f((int)size(2));
         for (int j = 0; j < 4; ++j) d[12 + j] = bits_f(valid[j] ? ref[j] : ~0);
     }
     wide.swap(q);

@@ -47,6 +47,7 @@ struct SceneDev {
     const float4* nodes;   // kNodeRows float4 per node (layouts in api.hip)
     const float4* tris;    // 3 x float4 per leaf-ordered triangle:
                            //   (v0, orig id), (v1, segment), (v2, light index or -1)
+    const float4* tri_axis;// 3 x float4 per leaf-ordered triangle: x, y, z of the three vertices, orig id
     const float4* nrm;     // 3 x float4 per leaf-ordered triangle, or NULL
     const int4* lights;    // [nlt]: (leaf tri, emitter index, area bits, orig id)
     const int* seg_emitter;// [S]: emitter index or -1
@@ -123,6 +124,41 @@ struct PathArgs {
     unsigned* grec_count;
     int grec_cap, grec_stride;
 };
+
+// Path streams (stream.hip): state of a batch of paths in dense lists.
+constexpr int kStreamGroups = 8;    // one per XCD
+constexpr int kStreamCount = 32;    // counters of a group lie 128 B apart
+constexpr unsigned kNoPath = 0xFFFFFFFFu;
+struct StreamArgs {
+    int k;                  // vertex of this launch (1..D+1)
+    int64_t q0;             // the batch: pixels [q0, q0 + nq) of the pass's chunk, all samples;
+    unsigned nq;            // path p = s nq + (q - q0)
+    // The batch forms kStreamGroups independent groups: tiles of kBlock paths
+    // in turn.  A group's part of every list starts at group * cap, and blocks
+    // b of a group (b mod kStreamGroups) process only its part.
+    unsigned cap;           // list entries per group
+    unsigned* count;        // [k-1][group][kStreamCount]: closest-hit rays of vertex k, shadow rays of
+                            // vertex k-1, chunks of them taken by the ray kernel
+    // closest-hit lists of odd and even vertices
+    float4* ray_o[2];       // origin, triangle left
+    float4* ray_d[2];       // direction, sampling density
+    float4* path[2];        // throughput, path
+    float4* path_s[2];      // throughput at sampling parameters (Russian roulette)
+    int4* hit;              // leaf triangle, u, v, t of the current list
+    float4* L;              // per path: radiance
+    // shadow rays of the last vertex
+    float4* sh_o;           // origin, triangle left
+    float4* sh_d;           // direction, distance bound
+    float4* sh_lt;          // contribution with the prefix throughput, path
+    float4* sh_c;           // contribution without it, light triangle
+    int* ovf;               // overflow stacks of the ray kernel
+};
+constexpr size_t kStreamPathBytes = 14 * sizeof(float4);
+size_t stream_fixed_bytes(int num_cu);
+StreamArgs stream_layout(unsigned char* p, int num_cu, int64_t npaths);
+// one colour or gradient forward pass over the pixels of a.pix_begin/pix_count in batches of batch_pixels
+hipError_t launch_stream_pass(int mode, const PathArgs& a, StreamArgs t, int64_t batch_pixels, int num_cu, hipStream_t st);
+size_t ray_stream_ovf_bytes(int blocks);
 
 size_t path_lds_bytes(int mode, int P, int frozen, int S, int nlt, int guide_kind = 0, int params_global = 0);
 int path_blocks_per_cu(int mode, size_t lds, int guide_kind = 0, int params_global = 0, int mat = 0);
