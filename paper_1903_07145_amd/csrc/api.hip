@@ -334,8 +334,7 @@ extern "C" ipt_status ipt_scene_build_ex(const float* verts, int64_t nv, const f
     if (e == hipSuccess) e = hipMalloc((void**)&s->d_err, sizeof(Counters));
     if (e == hipSuccess) e = hipMemsetAsync(s->d_err, 0, sizeof(Counters), st);
     if (e == hipSuccess)
-        e = hipMalloc((void**)&s->d_ovf_rays,
-                      sizeof(int) * (size_t)kOvfDepth * trace_rays_grid(s->num_cu) * kBlock);
+        e = hipMalloc((void**)&s->d_ovf_rays, ray_stream_ovf_bytes(batch_ray_blocks(s->num_cu)));
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) {
         ipt_scene_free(s);
@@ -839,8 +838,12 @@ extern "C" ipt_status ipt_trace_rays(ipt_scene_t s, const float* origins, const 
     if (!s || !origins || !dirs || !out_tri || !out_tuv) return fail(IPT_ERR_INVALID_ARG, "NULL argument");
     if (n < 0) return fail(IPT_ERR_INVALID_ARG, "n < 0");
     if (n == 0) return IPT_OK;
-    HIP_OK(launch_trace_rays(s->dev, origins, dirs, skip_tri, n, tmin, brute_force, s->nt, out_tri, out_tuv,
-                             s->d_ovf_rays, trace_rays_grid(s->num_cu), s->d_err, (hipStream_t)hip_stream));
+    hipStream_t st = (hipStream_t)hip_stream;
+    if (brute_force)
+        HIP_OK(launch_brute_rays(s->dev, origins, dirs, skip_tri, n, tmin, s->nt, out_tri, out_tuv, s->num_cu, st));
+    else
+        HIP_OK(launch_batch_rays(s->dev, origins, dirs, skip_tri, n, tmin, s->nt, out_tri, out_tuv, s->d_ovf_rays,
+                                 s->num_cu, s->d_err, st));
     return IPT_OK;
 }
 

@@ -180,9 +180,11 @@ hipError_t launch_adam(float* params, const float* grad, float* m, float* v, int
                        float lr, float b1, float b2, float eps, const float* scale,
                        const float* lo, const float* hi, const uint8_t* trainable,
                        hipStream_t st);
-hipError_t launch_trace_rays(const SceneDev& sc, const float* o, const float* d, const int* skip,
-                             int64_t n, float tmin, int brute, int64_t nt, int* out_tri,
-                             float* out_tuv, int* ovf, int grid, Counters* err, hipStream_t st);
-int trace_rays_grid(int num_cu);
+hipError_t launch_brute_rays(const SceneDev& sc, const float* o, const float* d, const int* skip, int64_t n, float tmin,
+                             int64_t nt, int* out_tri, float* out_tuv, int num_cu, hipStream_t st);
+int batch_ray_blocks(int num_cu);
+hipError_t launch_batch_rays(const SceneDev& sc, const float* o, const float* d, const int* skip, int64_t n, float tmin,
+                             int64_t nt, int* out_tri, float* out_tuv, int* ovf, int num_cu, Counters* err,
+                             hipStream_t st);
 
 }  // namespace ipt

@@ -196,6 +196,52 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kRayBloc
                  a.count_stats ? &a.err->k[MODE] : nullptr);
 }
 
+// Closest hits of a caller's rays.  Every gridDim-th 64 rays belong to a block
+// (runs of consecutive rays cost unequally: 0.75 ms for 4.9 M camera rays of the
+// apartment), its waves take chunks of them: 0.98 -> 0.68 ms.
+struct BatchRays {
+    const SceneDev* sc;
+    const float* o;
+    const float* d;
+    const int* skip;
+    int64_t nt;
+    int* out_tri;
+    float* out_tuv;
+    static __device__ __forceinline__ int64_t ray(unsigned i) {
+        return ((int64_t)(i >> 6) * gridDim.x + blockIdx.x) * 64 + (i & 63u);
+    }
+    __device__ __forceinline__ void load(unsigned i, V3& ro, V3& rd, float& tmax, int& skip0, int& skip1, bool& any) const {
+        const int64_t j = ray(i);
+        ro = v3(o[3 * j], o[3 * j + 1], o[3 * j + 2]);
+        rd = v3(d[3 * j], d[3 * j + 1], d[3 * j + 2]);
+        skip0 = (skip && skip[j] >= 0 && skip[j] < nt) ? sc->pos_of[skip[j]] : -1;
+        skip1 = -1;
+        tmax = __builtin_inff();
+        any = false;
+    }
+    __device__ __forceinline__ void store(unsigned i, bool, const Hit& h) const {
+        const int64_t j = ray(i);
+        out_tri[j] = h.tri >= 0 ? __float_as_int(sc->tris[3 * (int64_t)h.tri].w) : -1;
+        out_tuv[3 * j] = h.tri >= 0 ? h.t : 0.0f;
+        out_tuv[3 * j + 1] = h.u;
+        out_tuv[3 * j + 2] = h.v;
+    }
+};
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kRayBlocksPerCu, 8))) void batch_ray_kernel(
+    SceneDev sc, const float* o, const float* d, const int* skip, int64_t n, float tmin, int64_t nt,
+    int* out_tri, float* out_tuv, int* ovf, Counters* err) {
+    __shared__ int stk[kRayStack * kBlock];
+    __shared__ unsigned work;
+    if (threadIdx.x == 0) work = 0u;
+    __syncthreads();
+    const int64_t sets = (n + 63) / 64, mine = (sets - blockIdx.x + gridDim.x - 1) / gridDim.x;   // sets of 64 rays
+    const bool last = (sets - 1) % gridDim.x == blockIdx.x;
+    const unsigned own = (unsigned)(64 * mine - (last ? 64 * sets - n : 0));
+    const BatchRays src{&sc, o, d, skip, nt, out_tri, out_tuv};
+    trace_stream(sc, tmin, src, own, stk, ovf, (unsigned)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
+                 (unsigned)(kBlock / 64), &work, err, (KStats*)nullptr);
+}
+
 // Shading of vertex k for every closest-hit ray of the list.  Bound by memory
 // latency (78% of the lanes active; L1 waits 64-71% of the cycles): 8.5 and 13 ms of
 // the apartment step's two passes.  No spills (98-157 VGPRs), unlike the state
@@ -470,6 +516,17 @@ size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 }  // namespace
 
 size_t ray_stream_ovf_bytes(int blocks) { return sizeof(int) * (size_t)kRayOvf * blocks * kBlock; }
+
+int batch_ray_blocks(int num_cu) { return num_cu * kRayBlocksPerCu; }
+
+hipError_t launch_batch_rays(const SceneDev& sc, const float* o, const float* d, const int* skip, int64_t n, float tmin,
+                             int64_t nt, int* out_tri, float* out_tuv, int* ovf, int num_cu, Counters* err,
+                             hipStream_t st) {
+    const int64_t blocks = std::min<int64_t>(batch_ray_blocks(num_cu), (n + kBlock - 1) / kBlock);
+    hipLaunchKernelGGL(batch_ray_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, st, sc, o, d, skip, n, tmin, nt,
+                       out_tri, out_tuv, ovf, err);
+    return hipGetLastError();
+}
 
 size_t stream_fixed_bytes(int num_cu) {
     // counters, overflow stacks, and what the lists need beyond one entry per path

@@ -946,27 +946,15 @@ hipError_t launch_paths(int mode, const PathArgs& a, int grid, size_t lds, hipSt
 }
 
 // ---------------------------------------------------------------------------
-// Batch ray casting (hit parity and BVH checks).
+// Batch ray casting against every triangle (checks the BVH).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void trace_rays_kernel(SceneDev sc, const float* o, const float* d,
-                                                            const int* skip, int64_t n, float tmin, int brute,
-                                                            int64_t nt, int* out_tri, float* out_tuv, int* ovf,
-                                                            Counters* err) {
-    __shared__ int stk[kShortStack * kBlock];
-    Stack st;
-    st.lds = stk;
-    st.ovf = ovf;
-    st.tid = threadIdx.x;
-    st.gtid = blockIdx.x * kBlock + threadIdx.x;
-    st.gthreads = gridDim.x * kBlock;
-    st.overflow = false;
-    st.sp = 0;
-    Work wk{0u, 0u, 0u, 0u, 0u};
+__global__ __launch_bounds__(kBlock) void brute_rays_kernel(SceneDev sc, const float* o, const float* d,
+                                                            const int* skip, int64_t n, float tmin, int64_t nt,
+                                                            int* out_tri, float* out_tuv) {
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
         Ray r = make_ray(v3(o[3 * i], o[3 * i + 1], o[3 * i + 2]), v3(d[3 * i], d[3 * i + 1], d[3 * i + 2]));
         int sk = (skip && skip[i] >= 0 && skip[i] < nt) ? sc.pos_of[skip[i]] : -1;
-        Hit h = brute ? brute_closest(sc, nt, r, tmin, sk)
-                      : traverse(sc, r, tmin, __builtin_inff(), sk, -1, false, st, wk);
+        Hit h = brute_closest(sc, nt, r, tmin, sk);
         int orig = -1;
         if (h.tri >= 0) orig = __float_as_int(sc.tris[3 * h.tri].w);
         out_tri[i] = orig;
@@ -974,16 +962,12 @@ __global__ __launch_bounds__(kBlock) void trace_rays_kernel(SceneDev sc, const f
         out_tuv[3 * i + 1] = h.u;
         out_tuv[3 * i + 2] = h.v;
     }
-    if (st.overflow) atomicAdd(&err->overflow, 1ull);
 }
 
-int trace_rays_grid(int num_cu) { return num_cu * 4; }
-
-hipError_t launch_trace_rays(const SceneDev& sc, const float* o, const float* d, const int* skip, int64_t n,
-                             float tmin, int brute, int64_t nt, int* out_tri, float* out_tuv, int* ovf, int grid,
-                             Counters* err, hipStream_t st) {
-    hipLaunchKernelGGL(trace_rays_kernel, dim3(grid), dim3(kBlock), 0, st, sc, o, d, skip, n, tmin, brute, nt,
-                       out_tri, out_tuv, ovf, err);
+hipError_t launch_brute_rays(const SceneDev& sc, const float* o, const float* d, const int* skip, int64_t n, float tmin,
+                             int64_t nt, int* out_tri, float* out_tuv, int num_cu, hipStream_t st) {
+    hipLaunchKernelGGL(brute_rays_kernel, dim3(num_cu * 4), dim3(kBlock), 0, st, sc, o, d, skip, n, tmin, nt, out_tri,
+                       out_tuv);
     return hipGetLastError();
 }
 
