@@ -605,7 +605,7 @@ static ipt_status do_render(ipt_scene_t s, const ipt_cameras* cams, const float*
     a.pix_count = npix;
     split_samples(npix, o->spp, pl.grid, a.spc, a.nchunk);
     a.part = a.nchunk > 1 ? (float*)(ws + pl.off_part) : nullptr;
-    HIP_OK(launch_light_cdf(s->dev, a.sparams, (float*)(ws + pl.off_cdf), st));
+    HIP_OK(launch_light_cdf(s->dev, a.sparams, (float*)(ws + pl.off_cdf), (float*)(ws + pl.off_ovf), st));
     HIP_OK(launch_zero_u32(a.work, 1, st));
     size_t lds = path_lds_bytes(kColor, a.P, a.frozen, s->S, s->nlt, a.guide_kind, a.params_global);
     int grid = (int)std::min<int64_t>(pl.grid, (npix * a.nchunk + kBlock - 1) / kBlock);
@@ -657,7 +657,7 @@ static ipt_status do_grad(ipt_scene_t s, const ipt_cameras* cams, const float* p
         a.grec_cap = guide_capacity(o->guide);
         a.grec_stride = guide_record_stride(o->guide);
     }
-    HIP_OK(launch_light_cdf(s->dev, a.sparams, (float*)(ws + pl.off_cdf), st));
+    HIP_OK(launch_light_cdf(s->dev, a.sparams, (float*)(ws + pl.off_cdf), (float*)(ws + pl.off_ovf), st));
     size_t lds_f = path_lds_bytes(kGradFwd, a.P, a.frozen, s->S, s->nlt, a.guide_kind, a.params_global);
     size_t lds_r = path_lds_bytes(kReplay, a.P, a.frozen, s->S, s->nlt, 0, a.params_global);
     if (a.params_global) HIP_OK(launch_zero_u32((unsigned*)a.grad_part, 2 * a.grad_copies * a.P, st));
