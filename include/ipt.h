@@ -203,14 +203,14 @@ ipt_status ipt_render(ipt_scene_t scene, const ipt_cameras *cams, const float *p
 /* ipt_render for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
  * same image estimate with no workspace argument.  Its scratch (work counter,
- * light-selection table, traversal overflow stacks, per-chunk sample sums)
- * is a fixed 40 MiB device array inside the library, one per device, held
- * until the process ends; the call allocates nothing, host or device, and
- * launches at most 2 blocks per CU of the colour kernel.  All calls on one
+ * light-selection table, traversal overflow stacks, per-chunk sample sums, 40
+ * MiB; lists of path streams, 216 MiB) is a fixed device array inside the
+ * library, one per device, held until the process ends; the call allocates
+ * nothing, host or device.  All calls on one
  * device share that array, so calls that overlap on one device (concurrent
  * streams, threads) race and must be serialised by the caller.  Inputs and
  * outputs as for ipt_render (the debug outputs of opts included).  Errors:
- * as ipt_render, plus IPT_ERR_NOT_SUPPORTED when the scratch would exceed
+ * as ipt_render, plus IPT_ERR_NOT_SUPPORTED when the first part would exceed
  * 40 MiB (25 MiB of overflow stacks, up to 4.5 MiB of per-chunk sums and 8 B
  * per light triangle: scenes of more than about 1.4 million light
  * triangles) and IPT_ERR_INVALID_ARG when the scene was built on another

@@ -262,27 +262,31 @@ __device__ __forceinline__ void trace_stream(const SceneDev& sc, float tmin, con
             }
         }
         // ---- leaf phase ----
-        if (pend != kTravDone) {
-            const int code = ~pend;
-            const int first = code >> 3, last = first + (code & 7);
-            pend = kTravDone;
-            ntris += last - first + 1;
-            for (int i = first; i <= last; ++i) {
-                if (i == skip0 || i == skip1) continue;
-                const float4* row = sc.tri_axis + 3 * (size_t)(uint32_t)i;
-                const float4 X = row[r.kx], Y = row[r.ky], Z = row[r.kz];
-                float t, u, v;
-                if (!tri_isect_axes(ox, oy, oz, r.Sx, r.Sy, r.Sz, X, Y, Z, tmin, t, u, v)) continue;
-                const int orig = __float_as_int(X.w);
-                if (any) {
-                    if (t < tmax) {
-                        best.tri = i; best.t = t;
-                        cur = kTravDone;
-                        break;
+        // one triangle per pass for every lane that holds one; the wave leaves
+        // when none does
+        while (__builtin_amdgcn_ballot_w64(pend != kTravDone)) {
+            if (pend != kTravDone) {
+                const int code = ~pend;
+                const int i = code >> 3;
+                pend = (code & 7) ? ~(code + 7) : kTravDone;   // first + 1, count - 1
+                ++ntris;
+                if (i != skip0 && i != skip1) {
+                    const float4* row = sc.tri_axis + 3 * (size_t)(uint32_t)i;
+                    const float4 X = row[r.kx], Y = row[r.ky], Z = row[r.kz];
+                    float t, u, v;
+                    if (tri_isect_axes(ox, oy, oz, r.Sx, r.Sy, r.Sz, X, Y, Z, tmin, t, u, v)) {
+                        const int orig = __float_as_int(X.w);
+                        if (any) {
+                            if (t < tmax) {
+                                best.tri = i; best.t = t;
+                                cur = kTravDone;
+                                pend = kTravDone;
+                            }
+                        } else if (t < best.t || (t == best.t && orig < best_orig)) {
+                            best.tri = i; best.t = t; best.u = u; best.v = v;
+                            best_orig = orig;
+                        }
                     }
-                } else if (t < best.t || (t == best.t && orig < best_orig)) {
-                    best.tri = i; best.t = t; best.u = u; best.v = v;
-                    best_orig = orig;
                 }
             }
         }
