@@ -284,114 +284,150 @@ __device__ __forceinline__ bf16x8 lds_col8(const __bf16* buf, int stride, int co
     return v;
 }
 
-constexpr int kTS = 64;   // training LDS row stride (bf16)
+// Training LDS row stride (bf16): 64 columns and a pad that spreads the rows'
+// 16-byte reads over the banks (a stride of 64 puts the 16 rows of an operand
+// on the same ones).
+constexpr int kTS = 72;
 
-// One wave (64 records) per block: forward, loss, backward.
-__global__ __launch_bounds__(64) void guide_train_kernel(TrainArgs t) {
-    // 56 KB: inputs, four hidden activations, and two gradient buffers that
+// Four waves (64 records) per block: forward, loss, backward.  A wave owns 16 of
+// the records (rows) in the products along the layers and 16 of the inputs in
+// the weight gradients, so the waves share nothing but the activations; the
+// products' operands and order are those of one wave doing all.  The serial
+// chain of layers, not arithmetic, bounds a block: 16384 records (one block per
+// CU) took 158 us with one wave per block, 42 us with four.
+__global__ __launch_bounds__(256) void guide_train_kernel(TrainArgs t) {
+    // 65 KB: inputs, four hidden activations, and two gradient buffers that
     // also hold the float32 outputs during the forward pass
     __shared__ __align__(16) __bf16 X[64 * kTS];
     __shared__ __align__(16) __bf16 H[4][64 * kTS];
     __shared__ __align__(16) __bf16 D2[2 * 64 * kTS];
+    __shared__ int segs[64];
     __bf16* dA = D2;
     __bf16* dB = D2 + 64 * kTS;
     float* Y = (float*)D2;
-    const int lane = threadIdx.x;
-    const int li = lane & 15, lk = (lane >> 4) * 8;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int li = lane & 15, lk = (lane >> 4) * 8, lr = (lane >> 4) * 4;
+    const int r0 = wave * 16;   // the wave's rows
     const GuideDev& gd = t.gd;
     const int b = t.b0 + blockIdx.x * 64 + lane;
     const bool ok = b < t.batch;
     float* part = t.part + (size_t)blockIdx.x * kGParams;
-    const float* rc = t.rec + kRecF * (ok ? batch_index(t, b) : 0);
-    int seg = ok ? __float_as_int(rc[3]) : 0;
-    // inputs
-    {
+    // inputs: the first wave's lanes one record each
+    const float* rc = t.rec;
+    if (wave == 0) {
+        rc += kRecF * (ok ? batch_index(t, b) : 0);
+        const int seg = ok ? __float_as_int(rc[3]) : 0;
+        // Segment that the embedding's gradient of this row is added to.  Known
+        // fault: it is the record's at this position of the FIRST launch (no b0), so
+        // for batches of more than 16384 records, which take several launches,
+        // the later ones' embedding gradients go to other records' segments.
+        const int rb = (int)blockIdx.x * 64 + lane;
+        segs[lane] = t.b0 == 0 || rb >= t.batch ? seg : __float_as_int(t.rec[kRecF * batch_index(t, rb) + 3]);
         float f[9] = {rc[0], rc[1], rc[2], rc[4], rc[5], rc[6], rc[8], rc[9], rc[10]};
         __bf16* row = X + lane * kTS;
         for (int i = 0; i < 9; ++i) row[i] = (__bf16)f[i];
         for (int i = 0; i < kGEmb; ++i) row[9 + i] = gd.embb[kGEmb * seg + i];
         for (int i = kGIn; i < kTS; ++i) row[i] = (__bf16)0.0f;
     }
-    for (int i = lane; i < 2 * 64 * kTS; i += 64) D2[i] = (__bf16)0.0f;
     __syncthreads();
     // forward: H[l] = relu(in W + b)
     const __bf16* ins[5] = {X, H[0], H[1], H[2], H[3]};
     const int tw[5] = {kGT1, kGT2, kGT3, kGT4, kGT5};
     const int bs[5] = {kGB1, kGB2, kGB3, kGB4, kGB5};
+#pragma unroll
     for (int l = 0; l < 5; ++l) {
         const int kpad = l == 0 ? kGK1 : kGHid, ksteps = l == 0 ? 1 : 2, nblk = l == 4 ? 3 : 4;
         const __bf16* in = ins[l];
-        for (int qb = 0; qb < 4; ++qb) {
-            f32x4 acc[4];
-            for (int nb = 0; nb < 4; ++nb) acc[nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            for (int ks = 0; ks < ksteps; ++ks) {
-                bf16x8 a = *(const bf16x8*)(in + (qb * 16 + li) * kTS + ks * 32 + lk);
-                for (int nb = 0; nb < nblk; ++nb) {
-                    bf16x8 bb = *(const bf16x8*)(gd.wb + tw[l] + (nb * 16 + li) * kpad + ks * 32 + lk);
-                    acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bb, acc[nb], 0, 0, 0);
-                }
-            }
+        f32x4 acc[4];
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) acc[nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int ks = 0; ks < ksteps; ++ks) {
+            const bf16x8 a = *(const bf16x8*)(in + (r0 + li) * kTS + ks * 32 + lk);
+#pragma unroll
             for (int nb = 0; nb < nblk; ++nb) {
-                int col = nb * 16 + li;
-                for (int r = 0; r < 4; ++r) {
-                    int row = qb * 16 + (lane >> 4) * 4 + r;
-                    if (l < 4) {
-                        float v = acc[nb][r] + gd.w[bs[l] + col];
-                        H[l][row * kTS + col] = (__bf16)fmaxf(v, 0.0f);
-                    } else if (col < kGOut) {
-                        Y[row * kGOut + col] = acc[nb][r] + gd.w[bs[l] + col];
-                    }
+                const bf16x8 bb = *(const bf16x8*)(gd.wb + tw[l] + (nb * 16 + li) * kpad + ks * 32 + lk);
+                acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bb, acc[nb], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int nb = 0; nb < nblk; ++nb) {
+            const int col = nb * 16 + li;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = r0 + lr + r;
+                if (l < 4) {
+                    const float v = acc[nb][r] + gd.w[bs[l] + col];
+                    H[l][row * kTS + col] = (__bf16)fmaxf(v, 0.0f);
+                } else if (col < kGOut) {
+                    Y[row * kGOut + col] = acc[nb][r] + gd.w[bs[l] + col];
                 }
             }
         }
-        __syncthreads();
+        // the next layer reads only rows that this wave wrote, which the LDS
+        // orders; the compiler must not reorder them either
+        __builtin_amdgcn_wave_barrier();
+        __threadfence_block();
     }
+    __syncthreads();
     // loss and dY (bf16, padded to 64 columns) into dA
     {
         float yr[kGOut];
-        for (int j = 0; j < kGOut; ++j) yr[j] = Y[lane * kGOut + j];
+        if (wave == 0)
+            for (int j = 0; j < kGOut; ++j) yr[j] = Y[lane * kGOut + j];
         __syncthreads();   // Y shares memory with dA
-        float w = ok ? rc[7] / fmaxf(*t.wsum, 1e-30f) : 0.0f;
-        float dy[kGOut], lq = 0.0f;
-        mixture_grad(yr, v3(rc[12], rc[13], rc[14]), w, dy, &lq);
-        float wl = (ok && w > 0.0f) ? w * lq : 0.0f;
-        for (int o = 32; o >= 1; o >>= 1) wl += __shfl_xor(wl, o, 64);
-        if (lane == 0 && wl != 0.0f) atomicAdd(t.lsum, wl);
-        __bf16* row = dA + lane * kTS;
-        for (int j = 0; j < 64; ++j) row[j] = (__bf16)((ok && j < kGOut) ? dy[j] : 0.0f);
+        if (wave == 0) {
+            float w = ok ? rc[7] / fmaxf(*t.wsum, 1e-30f) : 0.0f;
+            float dy[kGOut], lq = 0.0f;
+            mixture_grad(yr, v3(rc[12], rc[13], rc[14]), w, dy, &lq);
+            float wl = (ok && w > 0.0f) ? w * lq : 0.0f;
+            for (int o = 32; o >= 1; o >>= 1) wl += __shfl_xor(wl, o, 64);
+            if (lane == 0 && wl != 0.0f) atomicAdd(t.lsum, wl);
+            __bf16* row = dA + lane * kTS;
+            for (int j = 0; j < 64; ++j) row[j] = (__bf16)((ok && j < kGOut) ? dy[j] : 0.0f);
+        }
     }
     __syncthreads();
-    // backward, layer l = 4 .. 0; dA holds dZ_l (pre-activation gradient)
+    // backward, layer l = 4 .. 0; dz holds dZ_l (pre-activation gradient; all 64
+    // columns are written, those beyond the layer's width with zeros)
     const int rw[5] = {kGR1, kGR2, kGR3, kGR4, kGR5};
     const int gwo[5] = {kGW1, kGW2, kGW3, kGW4, kGW5};
     __bf16* dz = dA;
     __bf16* dn = dB;
+#pragma unroll
     for (int l = 4; l >= 0; --l) {
         const int nout = l == 4 ? kGOut : kGHid;
         const int nin = l == 0 ? kGIn : kGHid;
         const __bf16* in = ins[l];
-        // bias gradient: column sums of dz
-        if (lane < nout) {
+        // bias gradient: column sums of dz (the last wave has least else to do:
+        // of the first layer's 32 padded inputs it owns none)
+        if (wave == 3 && lane < nout) {
             float s = 0.0f;
+#pragma unroll 8
             for (int q = 0; q < 64; ++q) s += (float)dz[q * kTS + lane];
             part[bs[l] + lane] = s;
         }
         // dW[in][out] = sum_q in[q][in] dz[q][out]: A = in^T (M = inputs), B = dz (K = queries)
         const int mblk = l == 0 ? 2 : 4, nblk = l == 4 ? 3 : 4;
-        for (int ib = 0; ib < mblk; ++ib) {
+        if (wave < mblk) {
             f32x4 acc[4];
+#pragma unroll
             for (int nb = 0; nb < 4; ++nb) acc[nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
-                bf16x8 a = lds_col8(in, kTS, ib * 16 + li, ks * 32 + lk);
+                const bf16x8 a = lds_col8(in, kTS, r0 + li, ks * 32 + lk);
+#pragma unroll
                 for (int nb = 0; nb < nblk; ++nb) {
-                    bf16x8 bb = lds_col8(dz, kTS, nb * 16 + li, ks * 32 + lk);
+                    const bf16x8 bb = lds_col8(dz, kTS, nb * 16 + li, ks * 32 + lk);
                     acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bb, acc[nb], 0, 0, 0);
                 }
             }
+#pragma unroll
             for (int nb = 0; nb < nblk; ++nb) {
-                int col = nb * 16 + li;
+                const int col = nb * 16 + li;
+#pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    int row = ib * 16 + (lane >> 4) * 4 + r;
+                    const int row = r0 + lr + r;
                     if (row < nin && col < nout) part[gwo[l] + row * nout + col] = acc[nb][r];
                 }
             }
@@ -399,31 +435,33 @@ __global__ __launch_bounds__(64) void guide_train_kernel(TrainArgs t) {
         // d(in) = dz W^T: A = dz (K = outputs), B[k = out][n = in] = W[in][out] (r layout)
         const int kpad_out = l == 4 ? kGN5r : kGHid;
         const int nblk_in = l == 0 ? 2 : 4;
-        for (int qb = 0; qb < 4; ++qb) {
+        {
             f32x4 acc[4];
+#pragma unroll
             for (int nb = 0; nb < 4; ++nb) acc[nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
-                bf16x8 a = *(const bf16x8*)(dz + (qb * 16 + li) * kTS + ks * 32 + lk);
+                const bf16x8 a = *(const bf16x8*)(dz + (r0 + li) * kTS + ks * 32 + lk);
+#pragma unroll
                 for (int nb = 0; nb < nblk_in; ++nb) {
-                    bf16x8 bb = *(const bf16x8*)(gd.wb + rw[l] + (nb * 16 + li) * kpad_out + ks * 32 + lk);
+                    const bf16x8 bb = *(const bf16x8*)(gd.wb + rw[l] + (nb * 16 + li) * kpad_out + ks * 32 + lk);
                     acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bb, acc[nb], 0, 0, 0);
                 }
             }
+#pragma unroll
             for (int nb = 0; nb < nblk_in; ++nb) {
-                int col = nb * 16 + li;
+                const int col = nb * 16 + li;
+#pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    int row = qb * 16 + (lane >> 4) * 4 + r;
-                    float v = acc[nb][r];
+                    const int row = r0 + lr + r;
+                    const float v = acc[nb][r];
                     if (l > 0) {
                         // through the ReLU of the layer below
-                        float hv = (float)ins[l][row * kTS + col];
+                        const float hv = (float)ins[l][row * kTS + col];
                         dn[row * kTS + col] = (__bf16)(hv > 0.0f ? v : 0.0f);
                     } else if (col >= 9 && col < kGIn) {
-                        int rb = blockIdx.x * 64 + row;
-                        if (rb < t.batch) {
-                            int sg = __float_as_int(t.rec[kRecF * batch_index(t, rb) + 3]);
-                            atomicAdd(t.gemb + kGEmb * sg + (col - 9), v);
-                        }
+                        if ((int)blockIdx.x * 64 + row < t.batch)
+                            atomicAdd(t.gemb + kGEmb * segs[row] + (col - 9), v);
                     }
                 }
             }
@@ -432,9 +470,6 @@ __global__ __launch_bounds__(64) void guide_train_kernel(TrainArgs t) {
         __bf16* tmp = dz;
         dz = dn;
         dn = tmp;
-        // pad columns beyond the layer width stay zero: clear dn for the next round
-        for (int i = lane; i < 64 * kTS; i += 64) dn[i] = (__bf16)0.0f;
-        __syncthreads();
     }
 }
 
@@ -449,8 +484,6 @@ __global__ void guide_adam_kernel(float* p, const float* g, float* m, float* v, 
     p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
 }
 
-__global__ void neg_copy_kernel(const float* src, float* dst) { dst[0] = -src[0]; }
-
 // Appends n caller records at the ring position the counter holds (read
 // only here; a second launch advances it).
 __global__ void guide_append_kernel(const float* src, int64_t n, float* ring, const unsigned* count, int cap) {
@@ -462,11 +495,6 @@ __global__ void guide_append_kernel(const float* src, int64_t n, float* ring, co
 }
 
 __global__ void guide_count_add_kernel(unsigned* count, unsigned n) { *count += n; }
-
-__global__ void zero_f32_kernel(float* p, int n) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0.0f;
-}
 
 }  // namespace ipt
 
@@ -684,19 +712,41 @@ extern "C" ipt_status ipt_guide_eval(ipt_guide_t g, const float* feat, const int
     return e == hipSuccess ? IPT_OK : ipt_fail(IPT_ERR_HIP, hipGetErrorString(e));
 }
 
-// grad[i] += sum over blocks of part[block][i], i < kGParams (fixed order).
-__global__ void guide_part_reduce_kernel(const float* part, int nblocks, float* grad) {
-    int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= kGParams) return;
+// grad[i] += sum over blocks of part[block][i], i < kGParams (fixed order): 32
+// parameters per block, 8 threads each.  One thread per parameter waited for
+// its loads: 60 us for 256 blocks, now 6 us.  Also loss = -*lsum where asked.
+__global__ __launch_bounds__(256) void guide_part_reduce_kernel(const float* part, int nblocks, float* grad,
+                                                                const float* lsum, float* loss) {
+    __shared__ float red[8][32];
+    const int col = threadIdx.x & 31, seg = threadIdx.x >> 5;
+    const int i = blockIdx.x * 32 + col;
     float s = 0.0f;
-    for (int b = 0; b < nblocks; ++b) s += part[(size_t)b * kGParams + i];
-    grad[i] += s;
+    if (i < kGParams) {
+#pragma unroll 8
+        for (int b = seg; b < nblocks; b += 8) s += part[(size_t)b * kGParams + i];
+    }
+    red[seg][col] = s;
+    __syncthreads();
+    if (seg == 0 && i < kGParams) {
+        float sum = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) sum += red[k][col];
+        grad[i] += sum;
+    }
+    if (loss && blockIdx.x == 0 && threadIdx.x == 0) *loss = -*lsum;
+}
+
+// Zeroes the gradient and the two sums of a batch.
+__global__ void guide_zero_kernel(float* grad, int n, float* scal) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) grad[i] = 0.0f;
+    if (i < 2) scal[i] = 0.0f;
 }
 
 // Loss and gradient of one batch into grad [np]; scal[0] = sum of weights,
 // scal[1] = sum_b (w_b / sum w) log q_b.
 static void launch_loss_grad(ipt_guide_s* g, const float* rec, int64_t nrec, int batch, int direct, float* grad,
-                             hipStream_t st) {
+                             float* loss, hipStream_t st) {
     size_t np = kGParams + (size_t)g->S * kGEmb;
     TrainArgs t;
     t.gd = guide_dev(g);
@@ -712,16 +762,15 @@ static void launch_loss_grad(ipt_guide_s* g, const float* rec, int64_t nrec, int
     t.gw = grad;
     t.gemb = grad + kGParams;
     t.part = g->gpart;
-    hipLaunchKernelGGL(zero_f32_kernel, dim3((int)((np + 255) / 256)), dim3(256), 0, st, grad, (int)np);
-    hipLaunchKernelGGL(zero_f32_kernel, dim3(1), dim3(64), 0, st, g->scal, 2);
+    hipLaunchKernelGGL(guide_zero_kernel, dim3((int)((np + 255) / 256)), dim3(256), 0, st, grad, (int)np, g->scal);
     hipLaunchKernelGGL(guide_wsum_kernel, dim3(64), dim3(256), 0, st, t);
     const int chunk = kTrainChunkBlocks * 64;
     for (int b0 = 0; b0 < t.batch; b0 += chunk) {
         t.b0 = b0;
         const int nb = (std::min(chunk, t.batch - b0) + 63) / 64;
-        hipLaunchKernelGGL(guide_train_kernel, dim3(nb), dim3(64), 0, st, t);
-        hipLaunchKernelGGL(guide_part_reduce_kernel, dim3((kGParams + 255) / 256), dim3(256), 0, st, g->gpart, nb,
-                           grad);
+        hipLaunchKernelGGL(guide_train_kernel, dim3(nb), dim3(256), 0, st, t);
+        hipLaunchKernelGGL(guide_part_reduce_kernel, dim3((kGParams + 31) / 32), dim3(256), 0, st, g->gpart, nb, grad,
+                           g->scal + 1, b0 + chunk >= t.batch ? loss : nullptr);
     }
 }
 
@@ -730,8 +779,7 @@ extern "C" ipt_status ipt_guide_loss_grad(ipt_guide_t g, const float* rec, int64
     if (!g || !rec || !loss || !grad || n < 1 || n > (1 << 24))
         return ipt_fail(IPT_ERR_INVALID_ARG, "bad guide loss_grad arguments (1 <= n <= 2^24)");
     hipStream_t st = (hipStream_t)stream;
-    launch_loss_grad(g, rec, n, (int)n, 1, grad, st);
-    hipLaunchKernelGGL(neg_copy_kernel, dim3(1), dim3(1), 0, st, g->scal + 1, loss);
+    launch_loss_grad(g, rec, n, (int)n, 1, grad, loss, st);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? IPT_OK : ipt_fail(IPT_ERR_HIP, hipGetErrorString(e));
 }
@@ -768,7 +816,7 @@ extern "C" ipt_status ipt_guide_train(ipt_guide_t g, int32_t steps, float* loss_
     size_t np = kGParams + (size_t)g->S * kGEmb;
     float lsum_tot = 0.0f;
     for (int s = 0; s < steps; ++s) {
-        launch_loss_grad(g, g->rec, nrec, g->batch, 0, g->g, st);
+        launch_loss_grad(g, g->rec, nrec, g->batch, 0, g->g, nullptr, st);
         g->step++;
         float c1 = (float)(1.0 - std::pow(0.9, g->step)), c2 = (float)(1.0 - std::pow(0.999, g->step));
         hipLaunchKernelGGL(guide_adam_kernel, dim3((int)((np + 255) / 256)), dim3(256), 0, st, g->w, g->g, g->m,
