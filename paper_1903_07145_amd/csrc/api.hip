@@ -78,8 +78,8 @@ struct ipt_scene_s {
 };
 
 // Four-child nodes (default): the binary tree's child-pair records are
-// collapsed and quantized on the host (bvh_wide.cpp) and uploaded in place of
-// the binary ones; *levels receives the number of node levels.
+// collapsed on the host (bvh_wide.cpp), quantized on the device and put in
+// place of the binary ones; *levels receives the number of node levels.
 static hipError_t collapse_bvh4(float4*& d_nodes, int64_t& nnodes, int* levels, hipStream_t st) {
     static_assert(kWideNone == kNone, "empty child slot marker");
     std::vector<float> pairs(16 * (size_t)nnodes);
@@ -88,11 +88,17 @@ static hipError_t collapse_bvh4(float4*& d_nodes, int64_t& nnodes, int* levels, 
     if (e != hipSuccess) return e;
     std::vector<float> wide;
     const int64_t n4 = collapse_wide(pairs, wide, levels);
-    if (kNodeQuant) quantize_wide(wide);
-    float4* d4 = nullptr;
-    e = hipMalloc((void**)&d4, sizeof(float) * wide.size());
-    if (e == hipSuccess) e = hipMemcpyAsync(d4, wide.data(), sizeof(float) * wide.size(), hipMemcpyHostToDevice, st);
+    float4 *up = nullptr, *d4 = nullptr;
+    e = hipMalloc((void**)&up, sizeof(float) * wide.size());
+    if (e == hipSuccess) e = hipMemcpyAsync(up, wide.data(), sizeof(float) * wide.size(), hipMemcpyHostToDevice, st);
+    if (kNodeQuant) {
+        if (e == hipSuccess) e = hipMalloc((void**)&d4, sizeof(float) * 16 * n4);
+        if (e == hipSuccess) e = launch_quantize_nodes((const float*)up, n4, (float*)d4, st);
+    } else {
+        std::swap(up, d4);
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
+    hipFree(up);
     if (e != hipSuccess) {
         hipFree(d4);
         return e;

@@ -19,6 +19,10 @@ struct GpuBvh {
 // an empty string on success, else a message (nothing is left allocated).
 std::string build_bvh_gpu(const float* d_verts, const int* d_tris, int64_t nt, hipStream_t st, GpuBvh& out);
 
+// Four-child float nodes (32 floats each) -> the quantized nodes the traversal
+// reads (16 floats each); n > 0.
+hipError_t launch_quantize_nodes(const float* wide, int64_t n, float* q, hipStream_t st);
+
 // Leaf-ordered triangle records (v0, orig id) (v1, segment) (v2, light index),
 // the same triangles by axis (taxis: x, y, z of the three vertices, id),
 // shading normals (when d_normals != NULL) and the inverse permutation
