@@ -58,8 +58,8 @@ def log(msg):
 # counters (VALU work, HBM traffic) are reported only while these still hash
 # to the profiled version
 KERNEL_SOURCES = ["paper_1903_07145_amd/csrc/" + f for f in
-                  ("trace.hip", "stream.hip", "ray_stream.h", "path_dev.h", "ipt_math.h", "ipt_internal.h", "guide_dev.h", "disney.h", "api.hip",
-                   "bvh_gpu.hip", "bvh_wide.cpp")] + \
+                  ("trace.hip", "stream.hip", "adjoint.hip", "ray_stream.h", "path_dev.h", "ipt_math.h", "ipt_internal.h", "guide_dev.h", "disney.h", "api.hip",
+                   "bvh_gpu.hip", "bvh_quant.h", "bvh_wide.cpp")] + \
                  ["paper_1903_07145_amd/build.py"]
 
 

@@ -119,7 +119,8 @@ struct PathArgs {
     int guide_kind;                // proposal sampled: 0 none, 1 network (bfloat16 MFMA), 2 network
                                    // (float32 VALU), 3 cached rows
     float gmix;                    // probability of sampling the guide
-    float4* ck_d;                  // guided: [(k-1)*spp + s][pix_count] (sampled direction, NEE density)
+    float4* ck_d;                  // guided, or for adjoint.hip: [(k-1)*spp + s][pix_count] sampled direction
+                                   // and, guided, the NEE density, else the roulette's factor
     float* grec;                   // training-record ring [cap][16] or NULL
     unsigned* grec_count;
     int grec_cap, grec_stride;
@@ -162,6 +163,8 @@ size_t ray_stream_ovf_bytes(int blocks);
 
 size_t path_lds_bytes(int mode, int P, int frozen, int S, int nlt, int guide_kind = 0, int params_global = 0);
 int path_blocks_per_cu(int mode, size_t lds, int guide_kind = 0, int params_global = 0, int mat = 0);
+// adjoint from the vertex records, on at most max_blocks blocks; *grid: how many (adjoint.hip)
+hipError_t launch_adjoint(const PathArgs& a, int max_blocks, int num_cu, int* grid, hipStream_t st);
 hipError_t launch_guide_records(const PathArgs& a, hipStream_t st);
 hipError_t launch_paths(int mode, const PathArgs& a, int grid, size_t lds, hipStream_t st);
 // guide handle internals (guide.hip)

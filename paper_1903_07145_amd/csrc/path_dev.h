@@ -436,6 +436,14 @@ __device__ __forceinline__ void camera_ray(const PathArgs& a, int view, float px
 __device__ __forceinline__ void lds_add(double* g, int i, float x) {
     if (x != 0.0f) atomicAdd(g + i, (double)x);
 }
+// n interleaved copies of the sums, [parameter][copy]; g points at the lane's copy.
+struct GradCopies {
+    double* g;
+    int n;
+};
+__device__ __forceinline__ void lds_add(const GradCopies& c, int i, float x) {
+    if (x != 0.0f) atomicAdd(c.g + i * c.n, (double)x);
+}
 
 // ---------------------------------------------------------------------------
 // Shading shared by all passes.
@@ -526,7 +534,8 @@ template <> struct MatNP<DMat> { static constexpr int value = kDisneyParams; };
 // gradient, for a channel weight w (the Lambert + GGX terms use the factors
 // spec, dspec kept from the evaluation; the Disney model its hand-written
 // reverse sweep).
-__device__ __forceinline__ void mat_grad(double* grad, int mb, const Mat& m, const Shade&, V3, V3 w, float spec,
+template <class G>
+__device__ __forceinline__ void mat_grad(G grad, int mb, const Mat& m, const Shade&, V3, V3 w, float spec,
                                          float dspec) {
     lds_add(grad, mb + 0, w.x * kInvPi);
     lds_add(grad, mb + 1, w.y * kInvPi);
@@ -536,12 +545,13 @@ __device__ __forceinline__ void mat_grad(double* grad, int mb, const Mat& m, con
     lds_add(grad, mb + 5, w.z * spec);
     lds_add(grad, mb + 6, dot(w, m.ks) * dspec);
 }
-__device__ __forceinline__ void mat_grad(double* grad, int mb, const DMat& m, const Shade& g, V3 wi, V3 w, float,
+template <class G>
+__device__ __forceinline__ void mat_grad(G grad, int mb, const DMat& m, const Shade& g, V3 wi, V3 w, float,
                                          float) {
-    float G[kDisneyParams];
-    disney_grad(m, disney_geom(g.ns, g.tx, g.ty, g.wo, wi), w, G);
+    float d[kDisneyParams];
+    disney_grad(m, disney_geom(g.ns, g.tx, g.ty, g.wo, wi), w, d);
 #pragma unroll
-    for (int j = 0; j < kDisneyParams; ++j) lds_add(grad, mb + j, G[j]);
+    for (int j = 0; j < kDisneyParams; ++j) lds_add(grad, mb + j, d[j]);
 }
 
 // MIS weight of an emitter hit at vertex k reached by a direction sampled
@@ -775,7 +785,7 @@ __device__ __forceinline__ V3 suffix_sweep(const PathArgs& a, int klast, int s, 
     for (int k = klast; k >= 1; --k) {
         size_t ck = ((size_t)(k - 1) * a.spp + s) * plane + q;
         float4 c = a.ck_c[ck], av = a.ck_a[ck];
-        a.ck_c[ck] = make_float4(R.x, R.y, R.z, 0.0f);
+        a.ck_c[ck] = make_float4(R.x, R.y, R.z, c.w);
         R = v3(c.x, c.y, c.z) + v3(av.x, av.y, av.z) * R;
     }
     return R;

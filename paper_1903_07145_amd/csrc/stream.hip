@@ -370,9 +370,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
                     }
                     V3 av = v3(0.0f, 0.0f, 0.0f);
                     uint32_t flags = 0;
+                    float rq = 1.0f;
                     cont = cs.ok && cs.alive;
                     if (cont) {
-                        float rq = 1.0f / cs.qrr;
+                        rq = 1.0f / cs.qrr;
                         av = cs.av * rq;
                         Ts = Ts * cs.ts * rq;
                         flags |= kCkCont;
@@ -382,8 +383,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
                     if (MODE == kGradFwd) {
                         st_stream(&a.ck_hit[ck], make_int4((int)((uint32_t)(g.tri + 1) | flags), hb.y, hb.z, hb.w));
                         st_stream(&a.ck_a[ck], make_float4(av.x, av.y, av.z, cs.pdf));
-                        if (a.guided) st_stream(&a.ck_d[ck], make_float4(cs.wi.x, cs.wi.y, cs.wi.z, pb_nee));
-                        st_stream(&a.ck_c[ck], make_float4(cpart.x, cpart.y, cpart.z, 0.0f));
+                        if (a.ck_d) st_stream(&a.ck_d[ck], make_float4(cs.wi.x, cs.wi.y, cs.wi.z, a.guided ? pb_nee : rq));
+                        st_stream(&a.ck_c[ck], make_float4(cpart.x, cpart.y, cpart.z, rq));
                     }
                 }
             }
