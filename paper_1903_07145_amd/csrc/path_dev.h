@@ -763,8 +763,8 @@ __device__ __forceinline__ ContS cont_finish_cached(const PathArgs& a, const Sha
     return cont_eval(a, g, m, ms, c.wi, pdf, c.lobe, u, k, Ts);
 }
 
-// Streaming store of one 16 B checkpoint record: the records are read again
-// only by a later kernel, so they should not displace the scene's nodes and
+// Streaming store or load of one 16 B record of a checkpoint or list: it is read
+// again only by a later kernel, so they should not displace the scene's nodes and
 // triangles in the caches.
 __device__ __forceinline__ void st_stream(float4* p, float4 v) {
     typedef float f4 __attribute__((ext_vector_type(4)));
@@ -775,6 +775,17 @@ __device__ __forceinline__ void st_stream(int4* p, int4 v) {
     typedef int i4 __attribute__((ext_vector_type(4)));
     const i4 x = {v.x, v.y, v.z, v.w};
     __builtin_nontemporal_store(x, reinterpret_cast<i4*>(p));
+}
+
+__device__ __forceinline__ float4 ld_stream(const float4* p) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    const f4 x = __builtin_nontemporal_load(reinterpret_cast<const f4*>(p));
+    return make_float4(x.x, x.y, x.z, x.w);
+}
+__device__ __forceinline__ int4 ld_stream(const int4* p) {
+    typedef int i4 __attribute__((ext_vector_type(4)));
+    const i4 x = __builtin_nontemporal_load(reinterpret_cast<const i4*>(p));
+    return make_int4(x.x, x.y, x.z, x.w);
 }
 
 // Backward sweep of the gradient forward pass: R_{k+1} into the c slot of
