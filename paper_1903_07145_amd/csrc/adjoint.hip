@@ -1,25 +1,25 @@
-// Adjoint (gfx950): the gradient of every path vertex from its records, a
-// vertex per lane.
+// Adjoint of a pass with a guide, Lambert + GGX (gfx950): the gradient of every path
+// vertex from its records, a vertex per lane.
 //
-// A lane that walks a path (replay_kernel in trace.hip) idles until the longest
-// path of its wave is done, and few vertices have a light sample that counts
-// (11% in the apartment): 36% of the lanes of an issued VALU instruction were
-// active (39% with the Disney model, whose lanes took new paths), and the
-// apartment's replay was bound by issue (VALU busy 97%).  But the vertices of a
-// path depend on each other only through the prefix throughput T_k, the suffix
-// radiance R_{k+1}, the incoming direction and its density, and the forward pass
-// keeps what these need: a_k (whose products are T), c_k (whose sweep is R), the
-// directions and densities.  So a wave takes a tile of paths, sweeps them once (a
-// path per lane, results in LDS), and then takes their vertices 64 at a time, in
-// the order of their index, so that a pass mostly holds one index and its reads
-// lie together; a tile has as many paths as fill whole passes.  Vertices with a
-// light sample that counts wait in a list until there are 64.  No block barrier:
-// the waves of a block share the parameters and the gradient sums.
+// A lane that walks a path (the replay kernels in trace.hip) idles until the
+// longest path of its wave is done, and in the part of a vertex's work whose light
+// sample does not count: 36-39% of the lanes of an issued VALU instruction are
+// active there.  But the vertices of a path depend on each other only through the
+// prefix throughput T_k, the suffix radiance R_{k+1}, the incoming direction and its
+// density, and with a guide the forward pass keeps what these need: a_k (whose
+// products are T), R, the directions and densities.  So a wave takes a tile of
+// paths, sweeps them once (a path per lane, results in LDS), and then takes their
+// vertices 64 at a time, in the order of their index, so that a pass mostly holds
+// one index and its reads lie together; a tile has as many paths as fill whole
+// passes.  Vertices with a light sample that counts wait in a list until there are
+// 64.  No block barrier: the waves of a block share the parameters and the gradient
+// sums.
 //
-// Measured, replay -> this kernel: apartment 13.0 -> 7.3 ms, with the Disney
-// model 5.4 -> 2.0, room 1.4 -> 1.05 (lanes active 73 - 78%, VALU busy 57 - 70%,
-// address unit 74 - 40%); the forward pass writes 16 B per vertex more for it,
-// 0.3 ms of the apartment's 45.
+// Measured on the guided room step, replay -> this kernel: 0.64 -> 0.41 ms.
+// Elsewhere the replay stays, although this kernel took 7.3 ms where it takes 13
+// (apartment; Disney model 2.0 and 5.4): without a guide it samples each direction
+// again, in other last bits than the forward pass has, which narrow lobes turn into
+// up to 4e-5 of the gradient, and so do the Disney model's weights here with a guide.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -30,12 +30,12 @@ namespace ipt {
 
 namespace {
 
-// Vertices of a tile: with more, fewer blocks fit into a CU's LDS (Disney
-// apartment 2.0 ms with 192, 3.1 with 256); with 128, sweeps cost more (apartment
-// 7.4 and 7.8 ms).
+// Vertices of a tile: with more, fewer blocks fit into a CU's LDS (256: 0.43 ms;
+// with many parameters 3.1 instead of 2.0); with 128, sweeps cost more (0.42).
 constexpr int kEntries = 192;
 constexpr int kLit = 127;                   // lit vertices: fewer than 64 wait, a pass adds at most 64
 constexpr int kWaves = kBlock / 64;
+constexpr int64_t kRec = 4;                 // ck_n with a guide
 constexpr int kMaxChunk = 1024;             // paths that a wave takes at a time (below 2^24)
 // LDS of a wave: T x, y, z, R x, y, z by vertex of the tile; the lit vertices'
 // w T and (vertex index << 24 | path of the chunk); the paths by length
@@ -50,8 +50,8 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // Interleaved copies of a block's gradient sums, within 8 KiB of LDS: an LDS
-// atomic takes 3 cycles per lane on one address, 3 / n on n copies in turn (room
-// 1.15 -> 1.05 ms with four; with 16 KiB a block fewer fits and it is 1.17).
+// atomic takes 3 cycles per lane on one address, 3 / n on n copies in turn (0.42 ->
+// 0.40 ms with four; with 16 KiB a block fewer fits and it is 0.43).
 int sum_copies(int P) {
     int c = 1;
     while (c < 8 && sizeof(double) * P * 2 * c <= 8 << 10) c *= 2;
@@ -78,10 +78,10 @@ __device__ __forceinline__ Hit hit_of(int4 rec) {
     return h;
 }
 
-template <int PG, int MAT, int GUIDED>
+template <int PG>
 __global__ __launch_bounds__(kBlock) void adjoint_kernel(PathArgs a, int chunk, int copies) {   // chunk: paths per chunk
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int NP = MatSel<MAT>::NP;
+    constexpr int MAT = 0, NP = MatSel<MAT>::NP;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     Lds lds;
     carve_lds<PG>(a, kColor, smem, lds);
@@ -148,8 +148,8 @@ __global__ __launch_bounds__(kBlock) void adjoint_kernel(PathArgs a, int chunk, 
                 if (id.pix >= 0 && id.pix < npix_img && !(a.mask && a.mask[(size_t)id.wi * a.spp + id.s] == 0)) {
                     counted = true;
                     const int64_t p = p0 + at + lane;
-                    const uint32_t f1 = (uint32_t)a.ck_hit[p].x;
-                    n = min(max(__float_as_int(a.ck_c[p].w), 0), levels);
+                    const uint32_t f1 = (uint32_t)a.ck_hit[kRec * p].x;
+                    n = min(max(__float_as_int(a.ck_c[kRec * p].w), 0), levels);
                     if (f1 & kCkDrop) n = 0;
                 }
             }
@@ -184,19 +184,18 @@ __global__ __launch_bounds__(kBlock) void adjoint_kernel(PathArgs a, int chunk, 
             off -= cnt;
             nvert += lane == 0 ? (uint32_t)nv : 0u;
             // ---- T and R of the vertices ----
-            V3 R = v3(0.0f, 0.0f, 0.0f);
             {
                 const int64_t p = p0 + at + lane;
                 // four vertices' loads at a time: one after the other their
                 // latencies were most of a tile's time
                 for (int k4 = levels; k4 >= 1; k4 -= 4) {
-                    float4 av[4], c[4];
+                    float4 av[4], R[4];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const int k = k4 - i;
                         if (k >= 1 && n >= k) {
-                            av[i] = a.ck_a[p + (int64_t)(k - 1) * stride];
-                            c[i] = a.ck_c[p + (int64_t)(k - 1) * stride];
+                            av[i] = a.ck_a[kRec * (p + (int64_t)(k - 1) * stride)];
+                            R[i] = a.ck_c[kRec * (p + (int64_t)(k - 1) * stride)];   // R_{k+1}
                         }
                     }
 #pragma unroll
@@ -205,21 +204,16 @@ __global__ __launch_bounds__(kBlock) void adjoint_kernel(PathArgs a, int chunk, 
                         const int ok = __builtin_amdgcn_readlane(off, max(k, 1) - 1);
                         if (k >= 1 && n >= k) {
                             float* e = ent + ok + rank;
-                            if (GUIDED) R = xyz(c[i]);   // the forward pass made the sweep
                             e[0] = av[i].x;
                             e[kEntries] = av[i].y;
                             e[2 * kEntries] = av[i].z;
-                            e[3 * kEntries] = R.x;
-                            e[4 * kEntries] = R.y;
-                            e[5 * kEntries] = R.z;
-                            R = xyz(c[i]) + xyz(av[i]) * R;
+                            e[3 * kEntries] = R[i].x;
+                            e[4 * kEntries] = R[i].y;
+                            e[5 * kEntries] = R[i].z;
                         }
                     }
                 }
             }
-            const bool bad = !GUIDED && n > 0 && !finite3(R);
-            if (bad) atomicAdd(&a.err->nonfinite, 1ull);
-            const uint64_t dropped = __ballot(bad);
             {
                 V3 T = v3(1.0f, 1.0f, 1.0f);
                 for (int k = 1; k <= levels; ++k) {
@@ -252,12 +246,12 @@ __global__ __launch_bounds__(kBlock) void adjoint_kernel(PathArgs a, int chunk, 
                     V3 wT = v3(0.0f, 0.0f, 0.0f);
                     int i = 0;
                     const int src = j < nv ? order[j - o] : 0;
-                    if (j < nv && !((dropped >> src) & 1ull)) {
+                    if (j < nv) {
                         i = base + src;
                         const Id id = path_of(i);
                         // everything that the vertex may need, at once: the branches
                         // below would each wait for a load of their own
-                        const int64_t ck = p0 + i + (int64_t)(k - 1) * stride, before = k > 1 ? ck - stride : ck;
+                        const int64_t ck = kRec * (p0 + i + (int64_t)(k - 1) * stride), before = k > 1 ? ck - kRec * stride : ck;
                         const int4 rec = a.ck_hit[ck];
                         const float4 din = a.ck_d[before], dk = a.ck_d[ck];
                         const float pdf_in = a.ck_a[before].w;
@@ -285,26 +279,20 @@ __global__ __launch_bounds__(kBlock) void adjoint_kernel(PathArgs a, int chunk, 
                                 }
                             }
                             if (flags & kCkCont) {
-                                // the sampled direction and the roulette's factor come from
-                                // the checkpoint; without a guide the density does not: f
-                                // and p of a narrow lobe agree only where they see the same
-                                // rounding of the frame
+                                // the sampled direction, its density and the roulette's
+                                // factor come from the records
                                 mat_frame<MAT>(g);
                                 const typename MatSel<MAT>::M m = mat_load<MAT>(lds.params, g.seg);
-                                const typename MatSel<MAT>::M ms = a.frozen ? mat_load<MAT>(lds.sparams, g.seg) : m;
                                 const V3 out = xyz(dk);
                                 const V3 Rn = v3(e[3 * kEntries], e[4 * kEntries], e[5 * kEntries]);   // R_{k+1}
-                                float rq = dk.w, spec = 0.0f, dspec = 0.0f;
+                                float rq = k > 1 ? a.ck_c[ck].w : 1.0f, spec = 0.0f, dspec = 0.0f;
                                 const V3 f = mat_f(m, g, out, spec, dspec);
-                                const float cg = dot(g.ns, out) / (GUIDED ? a.ck_a[ck].w : mat_pdf(ms, g, out));
-                                if (GUIDED) {
-                                    rq = k > 1 ? a.ck_c[ck].w : 1.0f;
-                                    if (k == 1 && a.rr_depth >= 0 && a.rr_depth <= 1) {
-                                        // the slot of vertex 1 holds the path's length; its roulette sees one weight
-                                        V3 fs = f;
-                                        if (a.frozen) fs = mat_f_only(ms, g, out);
-                                        rq = 1.0f / fminf(fmaxf(maxc(fs * cg), 0.1f), 0.95f);
-                                    }
+                                const float cg = dot(g.ns, out) / a.ck_a[ck].w;
+                                if (k == 1 && a.rr_depth >= 0 && a.rr_depth <= 1) {
+                                    // the slot of vertex 1 holds the path's length; its roulette sees one weight
+                                    V3 fs = f;
+                                    if (a.frozen) fs = mat_f_only(mat_load<MAT>(lds.sparams, g.seg), g, out);
+                                    rq = 1.0f / fminf(fmaxf(maxc(fs * cg), 0.1f), 0.95f);
                                 }
                                 mat_grad(grad, NP * g.seg, m, g, out, wT * Rn * (cg * rq), spec, dspec);
                             }
@@ -329,10 +317,10 @@ __global__ __launch_bounds__(kBlock) void adjoint_kernel(PathArgs a, int chunk, 
                         const V3 wT = v3(r[0], r[kLit], r[2 * kLit]);
                         const int ki = __float_as_int(r[3 * kLit]), k = ki >> 24, i = ki & 0xFFFFFF;
                         const Id id = path_of(i);
-                        const int64_t ck = p0 + i + (int64_t)(k - 1) * stride;
-                        const float4 din = a.ck_d[k > 1 ? ck - stride : ck];
+                        const int64_t ck = kRec * (p0 + i + (int64_t)(k - 1) * stride);
+                        const float4 din = a.ck_d[k > 1 ? ck - kRec * stride : ck];
                         const Hit hit = hit_of(a.ck_hit[ck]);
-                        const float pb = GUIDED ? a.ck_d[ck].w : -1.0f;   // with a guide: the combined density of wl
+                        const float pb = a.ck_d[ck].w;   // the combined density of wl
                         Shade g;
                         make_shade(sc, lds, hit, k > 1 ? xyz(din) : camera_dir(a, id.pix, id.pid), g);
                         mat_frame<MAT>(g);
@@ -391,23 +379,14 @@ hipError_t launch(K kern, const PathArgs& a, int max_blocks, int num_cu, size_t 
     return hipGetLastError();
 }
 
-template <int MAT>
-hipError_t launch_mat(const PathArgs& a, int max_blocks, int num_cu, size_t lds, int* grid, hipStream_t st) {
-    if (a.params_global)
-        return a.guided ? launch(adjoint_kernel<1, MAT, 1>, a, max_blocks, num_cu, lds, grid, st)
-                        : launch(adjoint_kernel<1, MAT, 0>, a, max_blocks, num_cu, lds, grid, st);
-    return a.guided ? launch(adjoint_kernel<0, MAT, 1>, a, max_blocks, num_cu, lds, grid, st)
-                    : launch(adjoint_kernel<0, MAT, 0>, a, max_blocks, num_cu, lds, grid, st);
-}
-
 }  // namespace
 
 hipError_t launch_adjoint(const PathArgs& a, int max_blocks, int num_cu, int* grid, hipStream_t st) {
     const size_t lds = path_lds_bytes(kColor, a.P, a.frozen, a.sc.S, a.sc.nlt, 0, a.params_global) -
                        sizeof(int) * kShortStack * kBlock + kWaves * kWaveLds +
                        (a.params_global ? 0 : sizeof(double) * a.P * sum_copies(a.P));
-    return a.mat == 1 ? launch_mat<1>(a, max_blocks, num_cu, lds, grid, st)
-                      : launch_mat<0>(a, max_blocks, num_cu, lds, grid, st);
+    return a.params_global ? launch(adjoint_kernel<1>, a, max_blocks, num_cu, lds, grid, st)
+                           : launch(adjoint_kernel<0>, a, max_blocks, num_cu, lds, grid, st);
 }
 
 }  // namespace ipt

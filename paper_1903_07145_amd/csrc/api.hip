@@ -459,7 +459,6 @@ struct Plan {
            off_part = 0, off_ck = 0, end_fixed = 0;
     int64_t chunk = 0;         // work pixels per gradient chunk
     size_t ck_per_pixel = 0;   // checkpoint bytes per work pixel
-    size_t ck_dense_per_pixel = 0;   // with the directions that adjoint.hip reads
 };
 
 // Persistent grid: blocks per CU from the occupancy calculator (at most 8),
@@ -511,16 +510,13 @@ static void make_plan(const ipt_scene_s* s, const ipt_render_opts* o, int64_t np
     pl.off_ck = off;
     pl.end_fixed = off;
     pl.ck_per_pixel = (size_t)(o->max_depth + 1) * o->spp * (sizeof(int4) + (guided ? 3 : 2) * sizeof(float4));
-    pl.ck_dense_per_pixel = (size_t)(o->max_depth + 1) * o->spp * (sizeof(int4) + 3 * sizeof(float4));
 }
 
 static size_t plan_min(const Plan& pl, int64_t npix) {
     int64_t c = std::min<int64_t>(npix, kBlock);
     return pl.end_fixed + 4 * 256 + (size_t)c * pl.ck_per_pixel;
 }
-static size_t plan_full(const Plan& pl, int64_t npix) {
-    return pl.end_fixed + 4 * 256 + (size_t)npix * pl.ck_dense_per_pixel;
-}
+static size_t plan_full(const Plan& pl, int64_t npix) { return pl.end_fixed + 4 * 256 + (size_t)npix * pl.ck_per_pixel; }
 
 // Path streams or the per-lane state machine?  Returns the pixels per batch of
 // streams that fit into `bytes` of scratch, 0 for the state machine.  Streams
@@ -644,33 +640,24 @@ static ipt_status do_grad(ipt_scene_t s, const ipt_cameras* cams, const float* p
     // pixels per chunk from the space for checkpoints; streams take at most a
     // quarter of the space where the checkpoints do not leave them more
     const size_t avail = ws_bytes > pl.end_fixed + 4 * 256 ? ws_bytes - pl.end_fixed - 4 * 256 : 0;
-    // The adjoint takes a vertex per lane (adjoint.hip), except in the mode that
-    // traces again and where not even one pixel's records fit.
-    bool dense = !o->replay_traverse;
-    size_t per_pixel = dense ? pl.ck_dense_per_pixel : pl.ck_per_pixel;
-    const size_t all_ck = (size_t)npix * per_pixel;
+    const size_t all_ck = (size_t)npix * pl.ck_per_pixel;
     int64_t batch = stream_batch(s, o, npix, std::max(avail / 4, avail - std::min(avail, all_ck)));
     size_t stream_bytes = batch > 0 ? 256 + al256(stream_fixed_bytes(s->num_cu) + kStreamPathBytes * (size_t)(batch * o->spp)) : 0;
-    int64_t chunk = (int64_t)((avail - stream_bytes) / per_pixel);
+    int64_t chunk = (int64_t)((avail - stream_bytes) / pl.ck_per_pixel);
     if (batch > 0 && chunk < std::min<int64_t>(npix, kBlock)) {
         batch = 0;
         stream_bytes = 0;
-        chunk = (int64_t)(avail / per_pixel);
-    }
-    if (chunk < 1 && dense) {
-        dense = false;
         chunk = (int64_t)(avail / pl.ck_per_pixel);
     }
     unsigned char* stream_ws = ws + ((ws_bytes - stream_bytes) & ~size_t(255));
-    if (chunk < npix && chunk > kBlock) chunk = (chunk / kBlock) * kBlock;
+    if (chunk < npix) chunk = (chunk / kBlock) * kBlock;
     chunk = std::min<int64_t>(chunk, npix);
     if (chunk < 1) return fail(IPT_ERR_WORKSPACE_TOO_SMALL, "workspace too small for one gradient chunk");
-    size_t rec = (size_t)(o->max_depth + 1) * o->spp * (size_t)chunk;
-    unsigned char* ck = ws + pl.off_ck;
-    a.ck_hit = (int4*)ck;
-    a.ck_a = (float4*)(ck + al256(rec * sizeof(int4)));
-    a.ck_c = (float4*)(ck + al256(rec * sizeof(int4)) + al256(rec * sizeof(float4)));
-    a.ck_d = a.guided || dense ? (float4*)(ck + al256(rec * sizeof(int4)) + 2 * al256(rec * sizeof(float4))) : nullptr;
+    a.ck_n = a.guided ? 4 : 3;
+    a.ck_hit = (int4*)(ws + pl.off_ck);
+    a.ck_a = (float4*)a.ck_hit + 1;
+    a.ck_c = (float4*)a.ck_hit + 2;
+    a.ck_d = a.guided ? (float4*)a.ck_hit + 3 : nullptr;
     if (a.guided) {
         a.grec = guide_records(o->guide);
         a.grec_count = guide_record_count(o->guide);
@@ -694,7 +681,7 @@ static ipt_status do_grad(ipt_scene_t s, const ipt_cameras* cams, const float* p
         }
         if (a.guided) HIP_OK(launch_guide_records(a, st));
         int grid_r = 0;
-        if (dense) {
+        if (a.guided && a.mat == 0) {   // adjoint.hip says why only these
             HIP_OK(timed_pass(s, kReplay, a, st, [&] { return launch_adjoint(a, pl.grid, s->num_cu, &grid_r, st); }));
         } else {
             // the replay pulls tiles, so it runs on as many blocks as are resident

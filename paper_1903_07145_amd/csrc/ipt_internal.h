@@ -97,9 +97,16 @@ struct PathArgs {
     float* path_L;                 // colour: [pixels*spp][3] per-path radiance or NULL
     float* dbg_vtx;                // colour: [pixels*spp][D+1][8] per-vertex record or NULL
     const uint8_t* mask;           // [pixels*spp] or NULL
-    int4* ck_hit;                  // checkpoint planes, [(k-1)*spp + s][pix_count]
-    float4* ck_a;
-    float4* ck_c;
+    // Vertex records, [(k-1)*spp + s][pix_count][ck_n]: the pointers are those of the
+    // first record's parts.  A record's parts lie together, since vertices of ended
+    // paths leave gaps: in planes of their own, the parts reached memory as pieces
+    // of 16 B (apartment: gradient forward pass 44.0 -> 43.1 ms, its replay 13.1 -> 13.6).
+    int ck_n;                      // 3, with a guide 4
+    int4* ck_hit;                  // leaf triangle + 1 and flags, u, v, t
+    float4* ck_a;                  // a_k, density of the continuation
+    float4* ck_c;                  // c_k, later R_{k+1}; vertex 1: the path's last vertex, others: the
+                                   // roulette's factor
+    float4* ck_d;                  // with a guide: sampled direction, NEE density
     const float* w;                // replay: adjoint image [pixels][3]
     double* grad_part;             // replay: [gridDim.x][P]
     unsigned* work;                // dynamic tile counter (zeroed before launch)
@@ -115,12 +122,10 @@ struct PathArgs {
     int mat;                       // material model: 0 Lambert + GGX, 1 Disney (selects the kernels)
     // learned proposal (one-sample MIS with BRDF sampling)
     GuideDev gd;
-    int guided;                    // a guide is attached (checkpoint plane ck_d is written)
+    int guided;                    // a guide is attached (ck_d is written)
     int guide_kind;                // proposal sampled: 0 none, 1 network (bfloat16 MFMA), 2 network
                                    // (float32 VALU), 3 cached rows
     float gmix;                    // probability of sampling the guide
-    float4* ck_d;                  // guided, or for adjoint.hip: [(k-1)*spp + s][pix_count] sampled direction
-                                   // and, guided, the NEE density, else the roulette's factor
     float* grec;                   // training-record ring [cap][16] or NULL
     unsigned* grec_count;
     int grec_cap, grec_stride;
@@ -163,7 +168,7 @@ size_t ray_stream_ovf_bytes(int blocks);
 
 size_t path_lds_bytes(int mode, int P, int frozen, int S, int nlt, int guide_kind = 0, int params_global = 0);
 int path_blocks_per_cu(int mode, size_t lds, int guide_kind = 0, int params_global = 0, int mat = 0);
-// adjoint from the vertex records, on at most max_blocks blocks; *grid: how many (adjoint.hip)
+// adjoint of a pass with a guide, on at most max_blocks blocks; *grid: how many (adjoint.hip)
 hipError_t launch_adjoint(const PathArgs& a, int max_blocks, int num_cu, int* grid, hipStream_t st);
 hipError_t launch_guide_records(const PathArgs& a, hipStream_t st);
 hipError_t launch_paths(int mode, const PathArgs& a, int grid, size_t lds, hipStream_t st);

@@ -788,13 +788,17 @@ __device__ __forceinline__ int4 ld_stream(const int4* p) {
     return make_int4(x.x, x.y, x.z, x.w);
 }
 
+// Index of the records of vertex k (1..) of sample s of the chunk's pixel q.
+__device__ __forceinline__ size_t ck_at(const PathArgs& a, int k, int s, int64_t q) {
+    return (((size_t)(k - 1) * a.spp + s) * (size_t)a.pix_count + q) * a.ck_n;
+}
+
 // Backward sweep of the gradient forward pass: R_{k+1} into the c slot of
 // vertex k; returns the path radiance.
 __device__ __forceinline__ V3 suffix_sweep(const PathArgs& a, int klast, int s, int64_t q) {
-    const size_t plane = (size_t)a.pix_count;
     V3 R = v3(0.0f, 0.0f, 0.0f);
     for (int k = klast; k >= 1; --k) {
-        size_t ck = ((size_t)(k - 1) * a.spp + s) * plane + q;
+        const size_t ck = ck_at(a, k, s, q);
         float4 c = a.ck_c[ck], av = a.ck_a[ck];
         a.ck_c[ck] = make_float4(R.x, R.y, R.z, c.w);
         R = v3(c.x, c.y, c.z) + v3(av.x, av.y, av.z) * R;

@@ -173,7 +173,7 @@ struct PathRays {
             if (MODE == kGradFwd) {
                 const int s = (int)(p / t->nq);
                 const int64_t q = t->q0 + (int64_t)(p - (unsigned)s * t->nq);
-                const size_t ck = ((size_t)(t->k - 2) * a->spp + s) * (size_t)a->pix_count + q;
+                const size_t ck = ck_at(*a, t->k - 1, s, q);
                 const float4 n = t->sh_c[j];
                 const float4 v = a->ck_c[ck];
                 a->ck_hit[ck].x |= (int)kCkVis;
@@ -245,7 +245,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kRayBloc
 }
 
 // Shading of vertex k for every closest-hit ray of the list.  Bound by memory
-// latency (78% of the lanes active; L1 waits 64-71% of the cycles): 8.5 and 13 ms of
+// latency (78% of the lanes active; L1 waits 64-71% of the cycles): 7.3 and 12 ms of
 // the apartment step's two passes.  No spills (98-157 VGPRs), unlike the state
 // machine's 41-51; a forced fourth or fifth wave per SIMD changed nothing (97.0 ms)
 // or spilled (102.2 ms).
@@ -259,7 +259,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     const SceneDev& sc = a.sc;
     const float* cdf = lds.lights_in_lds ? lds.cdf : a.cdf;
     const int4* lights = lds.lights_in_lds ? lds.lights : sc.lights;
-    const size_t plane = (size_t)a.pix_count;
     // the rounding of e1 u + e2 v in the state machine's variants
     constexpr int UV = MAT == 0 && (PG == 0 || GUIDE == 3) ? 2 : 1;
     const int k = t.k, D = a.D;
@@ -283,8 +282,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
         if (p != kNoPath) {
             const PathId id = path_id(a, t, p);
             const uint64_t pid = (uint64_t)id.pix * (uint64_t)a.spp + (uint64_t)id.s;
-            const size_t c1 = (size_t)id.s * plane + id.q;
-            const size_t ck = (size_t)(k - 1) * a.spp * plane + c1;
+            const size_t c1 = ck_at(a, 1, id.s, id.q);
+            const size_t ck = ck_at(a, k, id.s, id.q);
             const int4 hb = ld_stream(&t.hit[i]);
             Hit hr;
             hr.tri = hb.x;
@@ -295,7 +294,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
             int klast = k;
             bool end_path = true;
             if (hr.tri < 0) {
-                if (MODE == kGradFwd) st_stream(&a.ck_hit[ck], make_int4(0, 0, 0, 0));
+                if (MODE == kGradFwd) a.ck_hit[ck] = make_int4(0, 0, 0, 0);
                 klast = k - 1;   // a miss contributes nothing: the sweep starts below it
                 if (k == 1) t.L[p] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             } else {
@@ -326,9 +325,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
                     // x_{D+1} only counts its emission; a shading normal facing
                     // away ends the path
                     if (MODE == kGradFwd) {
-                        st_stream(&a.ck_hit[ck], make_int4(g.tri + 1, hb.y, hb.z, hb.w));
-                        st_stream(&a.ck_a[ck], make_float4(0.0f, 0.0f, 0.0f, 0.0f));
-                        st_stream(&a.ck_c[ck], make_float4(cpart.x, cpart.y, cpart.z, 0.0f));
+                        a.ck_hit[ck] = make_int4(g.tri + 1, hb.y, hb.z, hb.w);
+                        a.ck_a[ck] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                        a.ck_c[ck] = make_float4(cpart.x, cpart.y, cpart.z, 0.0f);
                     }
                 } else {
                     // ---- light sample and continuation of vertex k ----
@@ -383,10 +382,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
                     }
                     end_path = !cont;
                     if (MODE == kGradFwd) {
-                        st_stream(&a.ck_hit[ck], make_int4((int)((uint32_t)(g.tri + 1) | flags), hb.y, hb.z, hb.w));
-                        st_stream(&a.ck_a[ck], make_float4(av.x, av.y, av.z, cs.pdf));
-                        if (a.ck_d) st_stream(&a.ck_d[ck], make_float4(cs.wi.x, cs.wi.y, cs.wi.z, a.guided ? pb_nee : rq));
-                        st_stream(&a.ck_c[ck], make_float4(cpart.x, cpart.y, cpart.z, rq));
+                        a.ck_hit[ck] = make_int4((int)((uint32_t)(g.tri + 1) | flags), hb.y, hb.z, hb.w);
+                        a.ck_a[ck] = make_float4(av.x, av.y, av.z, cs.pdf);
+                        if (a.guided) a.ck_d[ck] = make_float4(cs.wi.x, cs.wi.y, cs.wi.z, pb_nee);
+                        a.ck_c[ck] = make_float4(cpart.x, cpart.y, cpart.z, rq);
                     }
                 }
             }
@@ -469,7 +468,7 @@ __global__ __launch_bounds__(kBlock) void stream_grad_end_kernel(PathArgs a, Str
     for (unsigned p = blockIdx.x * kBlock + threadIdx.x; p < n; p += gridDim.x * kBlock) {
         const PathId id = path_id(a, t, p);
         if (!id.ok) continue;
-        const size_t c1 = (size_t)id.s * (size_t)a.pix_count + id.q;
+        const size_t c1 = ck_at(a, 1, id.s, id.q);
         bool good = finite3(xyz(t.L[p]));
         if (a.guided) {
             const int klast = min(max(__float_as_int(a.ck_c[c1].w), 0), a.D + 1);
