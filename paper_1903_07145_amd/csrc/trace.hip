@@ -461,17 +461,15 @@ __device__ void replay_path(const PathArgs& a, const Lds& lds, Stack& st, Work& 
     const float* cdf = lds.lights_in_lds ? lds.cdf : a.cdf;
     const int4* lights = lds.lights_in_lds ? lds.lights : sc.lights;
     if ((uint32_t)a.ck_hit[ck_at(a, 1, s, q)].x & kCkDrop) return;
-    if (!a.guided) {
-        // the backward sweep, here rather than at the end of each path in the
-        // forward pass: every lane of the wave starts a path at once, so the
-        // sweeps' round trips to memory overlap instead of holding up a wave
-        // in which a few lanes end their paths
-        const int klast = min(max(__float_as_int(a.ck_c[ck_at(a, 1, s, q)].w), 0), a.D + 1);
-        const V3 R = suffix_sweep(a, klast, s, q);
-        if (!finite3(R)) {
-            atomicAdd(&a.err->nonfinite, 1ull);
-            return;
-        }
+    // the backward sweep, here rather than at the end of each path in the
+    // forward pass: every lane of the wave starts a path at once, so the
+    // sweeps' round trips to memory overlap instead of holding up a wave
+    // in which a few lanes end their paths
+    const int klast = min(max(__float_as_int(a.ck_c[ck_at(a, 1, s, q)].w), 0), a.D + 1);
+    const V3 R = suffix_sweep(a, klast, s, q);
+    if (!finite3(R)) {
+        atomicAdd(&a.err->nonfinite, 1ull);
+        return;
     }
     V3 T = v3(1.0f, 1.0f, 1.0f), Ts = T;
     float prev_pdf = 0.0f;
@@ -515,7 +513,6 @@ __device__ void replay_path(const PathArgs& a, const Lds& lds, Stack& st, Work& 
         const typename MatSel<MAT>::M ms = a.frozen ? mat_load<MAT>(lds.sparams, g.seg) : m;
         float u[8];
         vertex_uniforms(a.rng, pid, k, u);
-        float4 dk = a.guided ? a.ck_d[ck] : make_float4(0.0f, 0.0f, 0.0f, -1.0f);
         if (a.mis != 0 && sc.nlt > 0) {
             NeeS n = nee_setup(sc, cdf, lights, g, u);
             bool vis = false;
@@ -528,8 +525,7 @@ __device__ void replay_path(const PathArgs& a, const Lds& lds, Stack& st, Work& 
                 }
             }
             if (vis) {
-                // with a guide the forward pass stored the combined density of wl
-                NeeC nc = nee_contrib(a, lds, cdf, g, m, ms, n, dk.w);
+                NeeC nc = nee_contrib(a, lds, cdf, g, m, ms, n);
                 if (nc.valid) {
                     constexpr int NP = MatSel<MAT>::NP;
                     int mb = NP * g.seg, eb = NP * sc.S + 3 * n.lk;
@@ -543,14 +539,8 @@ __device__ void replay_path(const PathArgs& a, const Lds& lds, Stack& st, Work& 
             }
         }
         if (!(flags & kCkCont)) return;
-        ContS cs;
-        if (a.guided) {
-            // the sampled direction and its density come from the checkpoint
-            cs = cont_eval(a, g, m, ms, v3(dk.x, dk.y, dk.z), a.ck_a[ck].w, 0, u, k, Ts);
-        } else {
-            bool ug;
-            cs = cont_sample<0>(a, g, m, ms, u, k, Ts, nullptr, ug);
-        }
+        bool ug;
+        const ContS cs = cont_sample<0>(a, g, m, ms, u, k, Ts, nullptr, ug);
         float rq = 1.0f / cs.qrr;
         V3 wr = wT * Rn * (cs.g * rq);
         mat_grad(lds.grad, MatSel<MAT>::NP * g.seg, m, g, cs.wi, wr, cs.spec, cs.dspec);
