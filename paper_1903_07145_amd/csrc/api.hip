@@ -612,7 +612,6 @@ static ipt_status do_render(ipt_scene_t s, const ipt_cameras* cams, const float*
     split_samples(npix, o->spp, pl.grid, a.spc, a.nchunk);
     a.part = a.nchunk > 1 ? (float*)(ws + pl.off_part) : nullptr;
     HIP_OK(launch_light_cdf(s->dev, a.sparams, (float*)(ws + pl.off_cdf), (float*)(ws + pl.off_ovf), st));
-    HIP_OK(launch_zero_u32(a.work, 1, st));
     size_t lds = path_lds_bytes(kColor, a.P, a.frozen, s->S, s->nlt, a.guide_kind, a.params_global);
     int grid = (int)std::min<int64_t>(pl.grid, (npix * a.nchunk + kBlock - 1) / kBlock);
     const int64_t batch = stream_batch(s, o, npix, ws_bytes > pl.end_fixed ? ws_bytes - pl.end_fixed : 0);
@@ -622,8 +621,10 @@ static ipt_status do_render(ipt_scene_t s, const ipt_cameras* cams, const float*
         if (allow_profile) HIP_OK(timed_pass(s, kColor, a, st, pass));
         else HIP_OK(pass());
     } else if (allow_profile) {
+        HIP_OK(launch_zero_u32(a.work, 1, st));
         HIP_OK(timed_launch(s, kColor, a, std::max(1, grid), lds, st));
     } else {
+        HIP_OK(launch_zero_u32(a.work, 1, st));
         a.count_stats = 0;
         HIP_OK(launch_paths(kColor, a, std::max(1, grid), lds, st));
     }
@@ -633,7 +634,7 @@ static ipt_status do_render(ipt_scene_t s, const ipt_cameras* cams, const float*
 
 static ipt_status do_grad(ipt_scene_t s, const ipt_cameras* cams, const float* params, const float* sp,
                           const ipt_render_opts* o, int64_t npix, const float* w, float* grad, unsigned char* ws,
-                          size_t ws_bytes, const Plan& pl, hipStream_t st) {
+                          size_t ws_bytes, const Plan& pl, hipStream_t st, bool light_table = false) {
     PathArgs a = base_args(s, cams, params, sp, o, ws, pl);
     a.w = w;
     split_samples(npix, o->spp, pl.grid, a.spc, a.nchunk);
@@ -664,7 +665,9 @@ static ipt_status do_grad(ipt_scene_t s, const ipt_cameras* cams, const float* p
         a.grec_cap = guide_capacity(o->guide);
         a.grec_stride = guide_record_stride(o->guide);
     }
-    HIP_OK(launch_light_cdf(s->dev, a.sparams, (float*)(ws + pl.off_cdf), (float*)(ws + pl.off_ovf), st));
+    // (a colour pass of the same call may have left the light table)
+    if (!light_table)
+        HIP_OK(launch_light_cdf(s->dev, a.sparams, (float*)(ws + pl.off_cdf), (float*)(ws + pl.off_ovf), st));
     size_t lds_f = path_lds_bytes(kGradFwd, a.P, a.frozen, s->S, s->nlt, a.guide_kind, a.params_global);
     size_t lds_r = path_lds_bytes(kReplay, a.P, a.frozen, s->S, s->nlt, 0, a.params_global);
     if (a.params_global) HIP_OK(launch_zero_u32((unsigned*)a.grad_part, 2 * a.grad_copies * a.P, st));
@@ -824,7 +827,7 @@ extern "C" ipt_status ipt_loss_grad(ipt_scene_t s, const ipt_cameras* cams, cons
     stt = do_render(s, cams, params, nullptr, co, npa, img, ws, workspace_bytes, pl, st);
     if (stt != IPT_OK) return stt;
     HIP_OK(launch_loss_adjoint(img, target, 3 * npa, loss_kind, w, (float*)(ws + pl.off_loss), 1024, loss, st));
-    return do_grad(s, cams, params, nullptr, go, npb, w, grad, ws, workspace_bytes, pl, st);
+    return do_grad(s, cams, params, nullptr, go, npb, w, grad, ws, workspace_bytes, pl, st, true);
 }
 
 extern "C" ipt_status ipt_sgd_step(float* params, const float* grad, float* m, float* v, int32_t P, int32_t step,

@@ -2,6 +2,8 @@
 // adjoint image, block-partial gradient reduction, projected Adam.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "ipt_internal.h"
 
 namespace ipt {
@@ -216,6 +218,7 @@ __global__ __launch_bounds__(256) void loss_final_kernel(const float* partials, 
 
 hipError_t launch_loss_adjoint(const float* img, const float* target, int64_t n3, int kind, float* w,
                                float* partials, int nparts, float* loss, hipStream_t st) {
+    nparts = (int)std::max<int64_t>(1, std::min<int64_t>(nparts, (n3 + 255) / 256));   // further sums are 0
     hipLaunchKernelGGL(loss_kernel, dim3(nparts), dim3(256), 0, st, img, target, n3, kind, w, partials);
     hipLaunchKernelGGL(loss_final_kernel, dim3(1), dim3(256), 0, st, partials, nparts, n3, loss);
     return hipGetLastError();
