@@ -14,7 +14,7 @@
 //    a time by passes spread over blocks of 1024 triangles: bin counts and
 //    bounds are formed in LDS and merged with global atomics, one wave costs
 //    the 189 candidate planes (one slab per lane), the partition is stable
-//    (per-chunk left counts, prefix-summed on the host) and the child bounds
+//    (per-chunk left counts and their prefix sums) and the child bounds
 //    are reduced from the partitioned triangles;
 //  * a node of at most 1024 triangles is split by one block down to nodes of at
 //    most 64, which one wave each finishes: the triangle ids stay in LDS while
@@ -73,6 +73,7 @@ struct alignas(16) GNode {   // binary node while building
 struct LTask {               // a large node split at the current level
     int node, first, count, depth;
     float cblo[3], cbhi[3];  // centroid bounds
+    int chunk0, nchunk;      // its chunks
 };
 struct Chunk {
     int task, start, end, left_before;   // left_before: left triangles of the task's earlier chunks
@@ -390,6 +391,27 @@ __global__ __launch_bounds__(kTB) void k_part_count(const LTask* tasks, const Ch
         for (int j = 0; j < kWaves; ++j) s += sw[j];
         chunk_left[blockIdx.x] = s;
     }
+}
+
+// Chunks' left counts -> the left triangles before each chunk (one wave per task).
+// err[0] is set where they do not add up to the decision's.
+__global__ __launch_bounds__(64) void k_chunk_prefix(const LTask* tasks, const Decision* dec, const int* cleft,
+                                                     Chunk* chunks, int* err) {
+    const LTask t = tasks[blockIdx.x];
+    const int lane = threadIdx.x;
+    int carry = 0;
+    for (int c0 = 0; c0 < t.nchunk; c0 += 64) {
+        const int c = c0 + lane;
+        const int own = c < t.nchunk ? cleft[t.chunk0 + c] : 0;
+        int v = own;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int u = __shfl_up(v, o, 64);
+            if (lane >= o) v += u;
+        }
+        if (c < t.nchunk) chunks[t.chunk0 + c].left_before = carry + v - own;
+        carry += __shfl(v, 63, 64);
+    }
+    if (lane == 0 && (carry != dec[blockIdx.x].nleft || carry <= 0 || carry >= t.count)) atomicExch(err, 1);
 }
 
 // Stable partition of each chunk into idx_tmp, plus the bounds of both children
@@ -1025,68 +1047,61 @@ std::string build_bvh_gpu(const float* d_verts, const int* d_tris, int64_t nt, h
     if (!large.empty()) {
         const int64_t max_large = nt / (kSmallMax + 1) + 1;
         const int64_t max_chunks = nt / kChunk + max_large + 1;
-        ar.reserve(Arena::bytes<LTask>(max_large) + 2 * Arena::bytes<Chunk>(max_chunks) +
-                   Arena::bytes<unsigned>(max_large * kBinWords) + Arena::bytes<Decision>(max_large) +
-                   Arena::bytes<unsigned>(max_large * 24));
-        LTask* d_tasks = ar.carve<LTask>(max_large);
-        Chunk* d_chunks = ar.carve<Chunk>(max_chunks);
+        // one upload per level (tasks, chunks) and one download (error flag,
+        // decisions, child bounds): a small copy takes the host some 30 us
+        const size_t up_max = Arena::bytes<LTask>(max_large) + Arena::bytes<Chunk>(max_chunks);
+        const size_t down_max = 256 + Arena::bytes<Decision>(max_large) + Arena::bytes<unsigned>(max_large * 24);
+        ar.reserve(up_max + down_max + Arena::bytes<unsigned>(max_large * kBinWords) + Arena::bytes<int>(max_chunks));
+        char* d_up = ar.carve<char>(up_max);
+        char* d_down = ar.carve<char>(down_max);
         unsigned* d_bins = ar.carve<unsigned>(max_large * kBinWords);
-        Decision* d_dec = ar.carve<Decision>(max_large);
         int* d_cleft = ar.carve<int>(max_chunks);
-        unsigned* d_acc = ar.carve<unsigned>(max_large * 24);
         if (ar.err != hipSuccess) return std::string("BVH scratch: ") + hipGetErrorString(ar.err);
+        int* lflags = (int*)d_down;
+        hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(kTB), 0, st, lflags, (int64_t)4, 0);
         std::vector<Chunk> chunks;
-        std::vector<Decision> dec;
-        std::vector<int> cleft;
-        std::vector<unsigned> acc;
+        std::vector<char> up, down;
         while (!large.empty()) {
             const int ntask = (int)large.size();
             if (ntask > max_large) return "BVH build: too many large nodes in one level";
             chunks.clear();
-            std::vector<int> chunk0(ntask + 1);
             for (int i = 0; i < ntask; ++i) {
-                chunk0[i] = (int)chunks.size();
+                large[i].chunk0 = (int)chunks.size();
                 for (int s = large[i].first; s < large[i].first + large[i].count; s += kChunk)
                     chunks.push_back(Chunk{i, s, std::min(s + kChunk, large[i].first + large[i].count), 0});
+                large[i].nchunk = (int)chunks.size() - large[i].chunk0;
             }
-            chunk0[ntask] = (int)chunks.size();
             const int nch = (int)chunks.size();
             if (nch > max_chunks) return "BVH build: chunk list overflow";
-            BVH_HIP(hipMemcpyAsync(d_tasks, large.data(), sizeof(LTask) * ntask, hipMemcpyHostToDevice, st));
-            BVH_HIP(hipMemcpyAsync(d_chunks, chunks.data(), sizeof(Chunk) * nch, hipMemcpyHostToDevice, st));
+            const size_t at_chunks = Arena::bytes<LTask>(ntask), at_acc = 256 + Arena::bytes<Decision>(ntask);
+            LTask* d_tasks = (LTask*)d_up;
+            Chunk* d_chunks = (Chunk*)(d_up + at_chunks);
+            Decision* d_dec = (Decision*)(d_down + 256);
+            unsigned* d_acc = (unsigned*)(d_down + at_acc);
+            up.resize(at_chunks + sizeof(Chunk) * nch);
+            std::memcpy(up.data(), large.data(), sizeof(LTask) * ntask);
+            std::memcpy(up.data() + at_chunks, chunks.data(), sizeof(Chunk) * nch);
+            BVH_HIP(hipMemcpyAsync(d_up, up.data(), up.size(), hipMemcpyHostToDevice, st));
             hipLaunchKernelGGL(k_init_bins, dim3(blocks_for((int64_t)ntask * kBinWords)), dim3(kTB), 0, st, d_bins,
                                ntask);
             hipLaunchKernelGGL(k_bin_large, dim3(nch), dim3(kTB), 0, st, d_tasks, d_chunks, pb, idx, d_bins);
             hipLaunchKernelGGL(k_split_large, dim3(ntask), dim3(64), 0, st, d_tasks, d_bins, d_dec);
             hipLaunchKernelGGL(k_part_count, dim3(nch), dim3(kTB), 0, st, d_tasks, d_chunks, d_dec, pb, idx, d_cleft);
-            BVH_HIP(hipGetLastError());
-            dec.resize(ntask);
-            cleft.resize(nch);
-            BVH_HIP(hipMemcpyAsync(dec.data(), d_dec, sizeof(Decision) * ntask, hipMemcpyDeviceToHost, st));
-            BVH_HIP(hipMemcpyAsync(cleft.data(), d_cleft, sizeof(int) * nch, hipMemcpyDeviceToHost, st));
-            BVH_HIP(hipStreamSynchronize(st));
-            for (int i = 0; i < ntask; ++i) {
-                int sum = 0;
-                for (int c = chunk0[i]; c < chunk0[i + 1]; ++c) {
-                    chunks[c].left_before = sum;
-                    sum += cleft[c];
-                }
-                if (sum != dec[i].nleft || sum <= 0 || sum >= large[i].count)
-                    return "BVH build: inconsistent partition of a large node";
-            }
-            BVH_HIP(hipMemcpyAsync(d_chunks, chunks.data(), sizeof(Chunk) * nch, hipMemcpyHostToDevice, st));
+            hipLaunchKernelGGL(k_chunk_prefix, dim3(ntask), dim3(64), 0, st, d_tasks, d_dec, d_cleft, d_chunks, lflags);
             hipLaunchKernelGGL(k_init_acc, dim3(blocks_for(24 * (int64_t)ntask)), dim3(kTB), 0, st, d_acc,
                                2 * ntask);
             hipLaunchKernelGGL(k_scatter, dim3(nch), dim3(kTB), 0, st, d_tasks, d_chunks, d_dec, pb, idx, idx_tmp,
-                               d_acc, flags);
+                               d_acc, lflags);
             hipLaunchKernelGGL(k_copy_back, dim3(nch), dim3(kTB), 0, st, d_chunks, idx_tmp, idx);
             BVH_HIP(hipGetLastError());
-            acc.resize(24 * (size_t)ntask);
-            int hflags[4];
-            BVH_HIP(hipMemcpyAsync(acc.data(), d_acc, sizeof(unsigned) * acc.size(), hipMemcpyDeviceToHost, st));
-            BVH_HIP(hipMemcpyAsync(hflags, flags, sizeof(hflags), hipMemcpyDeviceToHost, st));
+            down.resize(at_acc + sizeof(unsigned) * 24 * (size_t)ntask);
+            BVH_HIP(hipMemcpyAsync(down.data(), d_down, down.size(), hipMemcpyDeviceToHost, st));
             BVH_HIP(hipStreamSynchronize(st));
-            if (hflags[0]) return "BVH build: partition position out of range";
+            int failed;
+            std::memcpy(&failed, down.data(), sizeof(int));
+            if (failed) return "BVH build: inconsistent partition of a large node";
+            const Decision* dec = (const Decision*)(down.data() + 256);
+            const unsigned* acc = (const unsigned*)(down.data() + at_acc);
             std::vector<LTask> next;
             for (int i = 0; i < ntask; ++i) {
                 const LTask& t = large[i];
