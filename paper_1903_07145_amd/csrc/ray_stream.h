@@ -27,6 +27,11 @@ constexpr int kRayRefill = 32;
 // at the end of a launch (apartment step 104.0 ms at 4, 102.5 at 8), more cost
 // atomics on the groups' counters (103.2 at 16, 103.6 at 32).
 constexpr int kRayChunks = 8;
+// Few rays are spread over all waves, at least this many to a wave: a wave lasts as
+// long as the phases of its lanes together.  Steps of 4096 / 16384 / 65536 paths of the
+// apartment, depth 7: 1.02 / 1.21 / 1.32 ms with 64 rays to a wave, 1.00 / 1.15 / 1.28
+// with 32, 0.94 / 1.08 / 1.27 with 8.
+constexpr unsigned kRayFew = 8;
 // Traversal stack: entries in LDS (24 KB per block, 5 blocks per CU), the rest
 // in global memory; as many in all as the state machine's stack, which the
 // scene build checks the tree against, and one for the bottom.
@@ -117,11 +122,16 @@ __device__ __forceinline__ void trace_stream(const SceneDev& sc, float tmin, con
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int gtid = blockIdx.x * kBlock + tid, gthreads = gridDim.x * kBlock;
-    // about kRayChunks per wave, of 64 to 512 rays
-    const unsigned chunk = min(512u, max(64u, (n / (kRayChunks * nwaves)) & ~63u));
+    // about kRayChunks per wave, of 64 to 512 rays; few rays over all waves
+    const unsigned chunk = n < 64u * nwaves ? max(kRayFew, (n + nwaves - 1) / nwaves)
+                                            : min(512u, max(64u, (n / (kRayChunks * nwaves)) & ~63u));
     const unsigned nchunks = (n + chunk - 1) / chunk;
     unsigned at = wave;                    // the wave's chunk
     auto next_chunk = [&]() {
+        if (nchunks <= nwaves) {
+            at = nchunks;
+            return;
+        }
         unsigned c = 0;
         if (lane == 0) c = atomicAdd(work, 1u);
         at = __builtin_amdgcn_readfirstlane(c) + nwaves;
