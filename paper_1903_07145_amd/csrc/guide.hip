@@ -317,12 +317,7 @@ __global__ __launch_bounds__(256) void guide_train_kernel(TrainArgs t) {
     if (wave == 0) {
         rc += kRecF * (ok ? batch_index(t, b) : 0);
         const int seg = ok ? __float_as_int(rc[3]) : 0;
-        // Segment that the embedding's gradient of this row is added to.  Known
-        // fault: it is the record's at this position of the FIRST launch (no b0), so
-        // for batches of more than 16384 records, which take several launches,
-        // the later ones' embedding gradients go to other records' segments.
-        const int rb = (int)blockIdx.x * 64 + lane;
-        segs[lane] = t.b0 == 0 || rb >= t.batch ? seg : __float_as_int(t.rec[kRecF * batch_index(t, rb) + 3]);
+        segs[lane] = seg;   // the embedding row that takes this record's input gradient
         float f[9] = {rc[0], rc[1], rc[2], rc[4], rc[5], rc[6], rc[8], rc[9], rc[10]};
         __bf16* row = X + lane * kTS;
         for (int i = 0; i < 9; ++i) row[i] = (__bf16)f[i];
@@ -460,7 +455,7 @@ __global__ __launch_bounds__(256) void guide_train_kernel(TrainArgs t) {
                         const float hv = (float)ins[l][row * kTS + col];
                         dn[row * kTS + col] = (__bf16)(hv > 0.0f ? v : 0.0f);
                     } else if (col >= 9 && col < kGIn) {
-                        if ((int)blockIdx.x * 64 + row < t.batch)
+                        if (t.b0 + (int)blockIdx.x * 64 + row < t.batch)
                             atomicAdd(t.gemb + kGEmb * segs[row] + (col - 9), v);
                     }
                 }
