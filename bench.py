@@ -36,10 +36,8 @@ HBM_PEAK_GBS = 8000.0
 VALU_WAVE_INST_PEAK = 256 * 4 * 2.4e9 / 4
 VALU_LANE_INST_PEAK = VALU_WAVE_INST_PEAK * 64
 TRI_B = 48
-# BVH node bytes read per visit, by (children, bytes per node): 4-wide nodes
-# with quantized boxes read their four float4 rows (64 B), with float boxes
-# seven of their eight (112 B); binary nodes 64 B
-NODE_READ_B = {(4, 64): 64, (4, 128): 112, (2, 64): 64}
+# BVH node bytes read per visit: all four float4 rows
+NODE_READ_B = 64
 # checkpoint traffic per path vertex: the gradient forward pass writes the hit
 # record, a and c (3 x 16 B); the backward sweep reads a and c back (32 B) and
 # writes the suffix radiance (16 B), in the forward pass when a guide collects
@@ -248,10 +246,8 @@ def main():
     log("step %.1f ms (wall %.1f ms): colour %.1f ms, grad fwd %.1f ms, replay %.1f ms" % (
         ms_step, 1e3 * wall / args.steps, ms_col, k_fwd["total_ms"] / args.steps, k_rep["total_ms"] / args.steps))
 
-    node_b = NODE_READ_B[(info["node_width"], info["node_bytes"])]
-
     def kbytes(k, extra_per_vertex):
-        return k["nodes"] * node_b + k["tris"] * TRI_B + k["vertices"] * extra_per_vertex
+        return k["nodes"] * NODE_READ_B + k["tris"] * TRI_B + k["vertices"] * extra_per_vertex
 
     per = {}
     sweep_fwd = CK_SWEEP_B if args.guide else 0

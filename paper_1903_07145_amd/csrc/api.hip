@@ -77,11 +77,10 @@ struct ipt_scene_s {
     std::vector<std::pair<hipEvent_t, hipEvent_t>> ev[3];
 };
 
-// Four-child nodes (default): the binary tree's child-pair records are
+// Four-child nodes: the binary tree's child-pair records are
 // collapsed on the host (bvh_wide.cpp), quantized on the device and put in
 // place of the binary ones; *levels receives the number of node levels.
 static hipError_t collapse_bvh4(float4*& d_nodes, int64_t& nnodes, int* levels, hipStream_t st) {
-    static_assert(kWideNone == kNone, "empty child slot marker");
     std::vector<float> pairs(16 * (size_t)nnodes);
     hipError_t e = hipMemcpyAsync(pairs.data(), d_nodes, sizeof(float) * pairs.size(), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -91,12 +90,8 @@ static hipError_t collapse_bvh4(float4*& d_nodes, int64_t& nnodes, int* levels, 
     float4 *up = nullptr, *d4 = nullptr;
     e = hipMalloc((void**)&up, sizeof(float) * wide.size());
     if (e == hipSuccess) e = hipMemcpyAsync(up, wide.data(), sizeof(float) * wide.size(), hipMemcpyHostToDevice, st);
-    if (kNodeQuant) {
-        if (e == hipSuccess) e = hipMalloc((void**)&d4, sizeof(float) * 16 * n4);
-        if (e == hipSuccess) e = launch_quantize_nodes((const float*)up, n4, (float*)d4, st);
-    } else {
-        std::swap(up, d4);
-    }
+    if (e == hipSuccess) e = hipMalloc((void**)&d4, sizeof(float4) * kNodeRows * n4);
+    if (e == hipSuccess) e = launch_quantize_nodes((const float*)up, n4, (float*)d4, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     hipFree(up);
     if (e != hipSuccess) {
@@ -311,12 +306,10 @@ extern "C" ipt_status ipt_scene_build_ex(const float* verts, int64_t nv, const f
         nnodes = bvh.num_nodes;
     }
     int levels = depth;   // node levels of the traversal's tree
-    if (kNodeWidth == 4) {
-        e = collapse_bvh4(s->d_nodes, nnodes, &levels, st);
-        if (e != hipSuccess) {
-            ipt_scene_free(s);
-            return fail(IPT_ERR_HIP, "BVH layout: %s", hipGetErrorString(e));
-        }
+    e = collapse_bvh4(s->d_nodes, nnodes, &levels, st);
+    if (e != hipSuccess) {
+        ipt_scene_free(s);
+        return fail(IPT_ERR_HIP, "BVH layout: %s", hipGetErrorString(e));
     }
     auto t1 = std::chrono::steady_clock::now();
     // a node pushes at most width - 1 entries, so the stack holds at most

@@ -8,7 +8,7 @@
 
 namespace ipt {
 
-constexpr int kWideNone = 0x7FFFFFFF;   // empty child slot (the kernels' kNone)
+constexpr int kWideNone = 0x7FFFFFFF;   // empty child slot
 
 // Child-pair records, 16 floats each (child 0 lo xyz, hi xyz; child 1 lo xyz,
 // hi xyz; the two references as int bits: inner record index, leaf code

@@ -11,22 +11,13 @@ namespace ipt {
 constexpr int kBlock = 256;       // threads per block of the path kernels
 constexpr int kShortStack = 16;   // per-lane LDS stack entries (power of two)
 constexpr int kOvfDepth = 48;     // per-lane global overflow entries
-constexpr int kNone = 0x7FFFFFFF; // empty child slot
-// BVH node width of the traversal: 4 (the binary tree collapsed into
-// four-child nodes on the host, bvh_wide.cpp) or 2 (the binary tree's 64 B
-// child-pair nodes)
-#ifndef IPT_NODE_WIDTH
-#define IPT_NODE_WIDTH 4
+// Nodes of the traversal: four children, quantized child boxes, 64 B
+// (bvh_quant.h has the layout).  Every traversal reads this layout and no other.
+#if (defined(IPT_NODE_WIDTH) && IPT_NODE_WIDTH != 4) || (defined(IPT_NODE_QUANT) && IPT_NODE_QUANT == 0)
+#error "the node layout is fixed: no binary nodes (IPT_NODE_WIDTH) or float boxes (IPT_NODE_QUANT)"
 #endif
-constexpr int kNodeWidth = IPT_NODE_WIDTH;
-// 4-wide nodes with quantized child boxes (64 B, four float4 loads per
-// visit) instead of float boxes (128 B, seven loads)
-#ifndef IPT_NODE_QUANT
-#define IPT_NODE_QUANT 1
-#endif
-constexpr int kNodeQuant = (IPT_NODE_WIDTH == 4) ? IPT_NODE_QUANT : 0;
-// float4 rows per node in the node array
-constexpr int kNodeRows = kNodeWidth == 4 ? (kNodeQuant ? 4 : 8) : 4;
+constexpr int kNodeWidth = 4;
+constexpr int kNodeRows = 4;      // float4 rows per node in the node array
 constexpr int kMaxDepth = 16;     // max scattering vertices per path
 constexpr int kMaxLdsLights = 1024;
 constexpr int kMaxLdsParams = 4096;  // larger parameter vectors stay in global memory
@@ -44,7 +35,7 @@ constexpr uint32_t kCkDrop = 1u << 30;   // (vertex 1) path dropped: non-finite
 
 // Device view of a built scene.
 struct SceneDev {
-    const float4* nodes;   // kNodeRows float4 per node (layouts in api.hip)
+    const float4* nodes;   // kNodeRows float4 per node
     const float4* tris;    // 3 x float4 per leaf-ordered triangle:
                            //   (v0, orig id), (v1, segment), (v2, light index or -1)
     const float4* tri_axis;// 3 x float4 per leaf-ordered triangle: x, y, z of the three vertices, orig id

@@ -221,69 +221,64 @@ __device__ bool traverse_resume(const SceneDev& sc, const Ray& r, float tmin, fl
             // the rest after the leaf phase (at least one leaf is pending,
             // so every pass of the outer loop makes progress)
             if (IPT_NODE_BREAK > 0 && __popcll(searching) <= IPT_NODE_BREAK && __any(pend != kTravDone)) break;
-            if (inner && kNodeWidth == 4) {
+            if (inner) {
                 // four children: the nearest hit next, the others pushed far to near
                 wk.nodes++;
                 const float inf = __builtin_inff();
                 float t[4];
                 int c[4];
-                if constexpr (kNodeQuant) {
-                    // quantized child boxes: a plane is origin + q 2^e, so its
-                    // slab distance is fma(q, 2^e / d, (origin - o) / d); the
-                    // direction's sign picks each axis's near and far byte rows.
-                    // The byte enters the fma as an fp16 operand of the
-                    // mixed-precision fma (one instruction per plane instead of
-                    // a conversion and an fma; the same value bit for bit)
-                    const float4* n = sc.nodes + 4 * (size_t)cur;
-                    const float4 h = n[0], qa = n[1], qb = n[2], cr = n[3];
-                    c[0] = __float_as_int(cr.x); c[1] = __float_as_int(cr.y);
-                    c[2] = __float_as_int(cr.z); c[3] = __float_as_int(cr.w);
-                    // the references are needed only after the sort; tie them
-                    // to this point so their load issues with the box rows
-                    __asm__ volatile("" :: "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(c[3]));
-                    const uint32_t ew = __float_as_uint(h.w);
-                    // A carries an extra 2^24: a byte q, widened to 16 bits, is
-                    // read as the fp16 subnormal q 2^-24, so the mixed-precision
-                    // fma forms q 2^e / d + B exactly, with no conversion
-                    const V3 A = v3(ldexpf(r.inv.x, (int)(ew & 0xffu) - 103),
-                                    ldexpf(r.inv.y, (int)((ew >> 8) & 0xffu) - 103),
-                                    ldexpf(r.inv.z, (int)((ew >> 16) & 0xffu) - 103));
-                    const V3 B = v3((h.x - r.o.x) * r.inv.x, (h.y - r.o.y) * r.inv.y, (h.z - r.o.z) * r.inv.z);
-                    const uint32_t xl = __float_as_uint(qa.x), xh = __float_as_uint(qa.y);
-                    const uint32_t yl = __float_as_uint(qa.z), yh = __float_as_uint(qa.w);
-                    const uint32_t zl = __float_as_uint(qb.x), zh = __float_as_uint(qb.y);
-                    const uint32_t xn = negx ? xh : xl, xf = negx ? xl : xh;
-                    const uint32_t yn = negy ? yh : yl, yf = negy ? yl : yh;
-                    const uint32_t zn = negz ? zh : zl, zf = negz ? zl : zh;
-                    const float tmx = best.t + sc.tmin;
-                    // 16-bit lanes of children 0 and 2, and of children 1 and 3
-                    const h2x e02[6] = {bytes02(xn), bytes02(xf), bytes02(yn), bytes02(yf), bytes02(zn), bytes02(zf)};
-                    const h2x e13[6] = {bytes13(xn), bytes13(xf), bytes13(yn), bytes13(yf), bytes13(zn), bytes13(zf)};
+                // quantized child boxes: a plane is origin + q 2^e, so its
+                // slab distance is fma(q, 2^e / d, (origin - o) / d); the
+                // direction's sign picks each axis's near and far byte rows.
+                // The exit distance gets a relative slack, so a triangle lying
+                // on a box face is never culled.  The best hit so far gets an
+                // absolute one (sc.tmin): the triangle test's t carries an error
+                // of the order of the rounding of the scene coordinates, not of
+                // t, so without it a flat box could be culled against a hit
+                // whose t came out a few ulps of the coordinates short, and a
+                // tie between coplanar triangles would be decided by the tree
+                // instead of by the tie rule.
+                // The byte enters the fma as an fp16 operand of the
+                // mixed-precision fma (one instruction per plane instead of
+                // a conversion and an fma; the same value bit for bit)
+                const float4* n = sc.nodes + 4 * (size_t)cur;
+                const float4 h = n[0], qa = n[1], qb = n[2], cr = n[3];
+                c[0] = __float_as_int(cr.x); c[1] = __float_as_int(cr.y);
+                c[2] = __float_as_int(cr.z); c[3] = __float_as_int(cr.w);
+                // the references are needed only after the sort; tie them
+                // to this point so their load issues with the box rows
+                __asm__ volatile("" :: "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(c[3]));
+                const uint32_t ew = __float_as_uint(h.w);
+                // A carries an extra 2^24: a byte q, widened to 16 bits, is
+                // read as the fp16 subnormal q 2^-24, so the mixed-precision
+                // fma forms q 2^e / d + B exactly, with no conversion
+                const V3 A = v3(ldexpf(r.inv.x, (int)(ew & 0xffu) - 103),
+                                ldexpf(r.inv.y, (int)((ew >> 8) & 0xffu) - 103),
+                                ldexpf(r.inv.z, (int)((ew >> 16) & 0xffu) - 103));
+                const V3 B = v3((h.x - r.o.x) * r.inv.x, (h.y - r.o.y) * r.inv.y, (h.z - r.o.z) * r.inv.z);
+                const uint32_t xl = __float_as_uint(qa.x), xh = __float_as_uint(qa.y);
+                const uint32_t yl = __float_as_uint(qa.z), yh = __float_as_uint(qa.w);
+                const uint32_t zl = __float_as_uint(qb.x), zh = __float_as_uint(qb.y);
+                const uint32_t xn = negx ? xh : xl, xf = negx ? xl : xh;
+                const uint32_t yn = negy ? yh : yl, yf = negy ? yl : yh;
+                const uint32_t zn = negz ? zh : zl, zf = negz ? zl : zh;
+                const float tmx = best.t + sc.tmin;
+                // 16-bit lanes of children 0 and 2, and of children 1 and 3
+                const h2x e02[6] = {bytes02(xn), bytes02(xf), bytes02(yn), bytes02(yf), bytes02(zn), bytes02(zf)};
+                const h2x e13[6] = {bytes13(xn), bytes13(xf), bytes13(yn), bytes13(yf), bytes13(zn), bytes13(zf)};
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const h2x* e = (i & 1) ? e13 : e02;
-                        const int hi = i >> 1;
-                        const float nx = fmaf((float)(hi ? e[0].y : e[0].x), A.x, B.x);
-                        const float fx = fmaf((float)(hi ? e[1].y : e[1].x), A.x, B.x);
-                        const float ny = fmaf((float)(hi ? e[2].y : e[2].x), A.y, B.y);
-                        const float fy = fmaf((float)(hi ? e[3].y : e[3].x), A.y, B.y);
-                        const float nz = fmaf((float)(hi ? e[4].y : e[4].x), A.z, B.z);
-                        const float fz = fmaf((float)(hi ? e[5].y : e[5].x), A.z, B.z);
-                        const float tn = fmaxf(fmaxf(nx, ny), fmaxf(nz, tmin));
-                        const float tf = fminf(fminf(fx, fy), fminf(fz, tmx));
-                        t[i] = tn <= tf * 1.0000005f ? tn : inf;
-                    }
-                } else {
-                    // float child boxes; an empty slot's box is +inf on every
-                    // axis, so its entry distance is +inf and it sorts last
-                    const float4* n = sc.nodes + 8 * (size_t)cur;
-                    const float4 lx = n[0], hx = n[1], ly = n[2], hy = n[3], lz = n[4], hz = n[5], cr = n[6];
-                    c[0] = __float_as_int(cr.x); c[1] = __float_as_int(cr.y);
-                    c[2] = __float_as_int(cr.z); c[3] = __float_as_int(cr.w);
-                    t[0] = box_entry(r, v3(lx.x, ly.x, lz.x), v3(hx.x, hy.x, hz.x), tmin, best.t, sc.tmin);
-                    t[1] = box_entry(r, v3(lx.y, ly.y, lz.y), v3(hx.y, hy.y, hz.y), tmin, best.t, sc.tmin);
-                    t[2] = box_entry(r, v3(lx.z, ly.z, lz.z), v3(hx.z, hy.z, hz.z), tmin, best.t, sc.tmin);
-                    t[3] = box_entry(r, v3(lx.w, ly.w, lz.w), v3(hx.w, hy.w, hz.w), tmin, best.t, sc.tmin);
+                for (int i = 0; i < 4; ++i) {
+                    const h2x* e = (i & 1) ? e13 : e02;
+                    const int hi = i >> 1;
+                    const float nx = fmaf((float)(hi ? e[0].y : e[0].x), A.x, B.x);
+                    const float fx = fmaf((float)(hi ? e[1].y : e[1].x), A.x, B.x);
+                    const float ny = fmaf((float)(hi ? e[2].y : e[2].x), A.y, B.y);
+                    const float fy = fmaf((float)(hi ? e[3].y : e[3].x), A.y, B.y);
+                    const float nz = fmaf((float)(hi ? e[4].y : e[4].x), A.z, B.z);
+                    const float fz = fmaf((float)(hi ? e[5].y : e[5].x), A.z, B.z);
+                    const float tn = fmaxf(fmaxf(nx, ny), fmaxf(nz, tmin));
+                    const float tf = fminf(fminf(fx, fy), fminf(fz, tmx));
+                    t[i] = tn <= tf * 1.0000005f ? tn : inf;
                 }
                 // sorting network on (t, child) with selects, no branches;
                 // equal distances keep their slot order
@@ -303,27 +298,6 @@ __device__ bool traverse_resume(const SceneDev& sc, const Ray& r, float tmin, fl
                     const int nf = (t[1] < inf ? 1 : 0) + (t[2] < inf ? 1 : 0) + (t[3] < inf ? 1 : 0);
                     st.push_upto3(nf, nf == 3 ? c[3] : (nf == 2 ? c[2] : c[1]), nf == 3 ? c[2] : c[1], c[1]);
                     cur = c[0];
-                } else {
-                    cur = next_from_stack();
-                }
-            } else if (inner) {
-                wk.nodes++;
-                const float4* n = sc.nodes + 4 * (size_t)cur;
-                float4 n0 = n[0], n1 = n[1], n2 = n[2], n3 = n[3];
-                int c0 = __float_as_int(n3.x), c1 = __float_as_int(n3.y);
-                float t0 = box_entry(r, v3(n0.x, n0.y, n0.z), v3(n0.w, n1.x, n1.y), tmin, best.t, sc.tmin);
-                float t1 = box_entry(r, v3(n1.z, n1.w, n2.x), v3(n2.y, n2.z, n2.w), tmin, best.t, sc.tmin);
-                // box_entry returns +inf on a miss; best.t may itself be +inf
-                bool h0 = t0 < __builtin_inff();
-                bool h1 = (c1 != kNone) && t1 < __builtin_inff();
-                if (h0 && h1) {
-                    bool first0 = t0 <= t1;
-                    st.push(first0 ? c1 : c0);
-                    cur = first0 ? c0 : c1;
-                } else if (h0) {
-                    cur = c0;
-                } else if (h1) {
-                    cur = c1;
                 } else {
                     cur = next_from_stack();
                 }
