@@ -186,7 +186,12 @@ ipt_status ipt_scene_info(ipt_scene_t scene, ipt_scene_info_t *out);
 
 /* Workspace bytes for ipt_render / ipt_render_grad / ipt_loss_grad with these
  * options: *min_bytes lets the gradient run in chunks; *full_bytes keeps the
- * vertex checkpoints of every gradient path at once. */
+ * vertex checkpoints of every gradient path at once, and the path streams'
+ * lists (224 B per path, of at most 40 Mi paths, and some 50 MiB), without
+ * which a pass takes up to 4 times as long.  A colour pass needs no
+ * checkpoints: a query with max_depth 1 stands for it.  ipt_loss_grad takes at
+ * least the gradient options' *min_bytes; give it the larger of the gradient
+ * options' *full_bytes and the colour pass's where the latter has more samples. */
 ipt_status ipt_workspace_query(ipt_scene_t scene, const ipt_cameras *cams,
                                const ipt_render_opts *opts, size_t *min_bytes,
                                size_t *full_bytes);

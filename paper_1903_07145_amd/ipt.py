@@ -304,6 +304,12 @@ class Scene:
                   image=None):
         loss = loss if loss is not None else torch.empty(1, dtype=torch.float32, device="cuda")
         grad = grad if grad is not None else torch.empty(self.P, dtype=torch.float32, device="cuda")
+        if color_opts.spp > grad_opts.spp:
+            # the colour pass's lists may need more than the gradient's records and lists; it keeps no vertex
+            # records, which the query at depth 1 stands for
+            co = RenderOpts.from_buffer_copy(color_opts)
+            co.max_depth = 1
+            self.workspace(dcams, co)
         ws = self.workspace(dcams, grad_opts)
         C = _cams_struct(dcams)
         _check(lib().ipt_loss_grad(self.handle, ctypes.byref(C), _ptr(params), _ptr(target),
