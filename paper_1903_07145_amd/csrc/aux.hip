@@ -273,6 +273,8 @@ hipError_t launch_colour_reduce(const float* part, int nchunk, int64_t pix_count
     return hipGetLastError();
 }
 
+constexpr int kFlatParams = 1 << 14;
+
 // grad[i] (+)= sum_b part[b][i] in a fixed order (deterministic): 8 parameters
 // per block, each summed by 32 threads over every 32nd row and a tree.  One
 // thread per parameter waited for a load per row: 196 us for 1024 rows, now
@@ -296,8 +298,28 @@ __global__ __launch_bounds__(256) void grad_reduce_kernel(const double* part, in
     if (row == 0 && i < P) grad[i] = accumulate ? (float)((double)grad[i] + red[0][col]) : (float)red[0][col];
 }
 
+// The same for many parameters, a thread each: the reads of a row are contiguous and
+// there are threads enough to wait for them.
+__global__ __launch_bounds__(256) void grad_reduce_flat_kernel(const double* part, int nblocks, int P, float* grad,
+                                                               int accumulate) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= P) return;
+    double s = 0.0;
+#pragma unroll 8
+    for (int b = 0; b < nblocks; ++b) s += part[(size_t)b * P + i];
+    grad[i] = accumulate ? (float)((double)grad[i] + s) : (float)s;
+}
+
 hipError_t launch_grad_reduce(const double* part, int nblocks, int P, float* grad, int accumulate,
                               hipStream_t st) {
+    // gradient of 8 pixels by rows of 32 threads / by one thread per parameter: 90 / 117 us
+    // with 4203 parameters, 123 / 132 with 11903, 148 / 134 with 16383, 235 / 170 with
+    // 350 thousand, 1063 / 208 with 14 million (two rows, which leave most of 32 threads idle)
+    if (P >= kFlatParams) {
+        hipLaunchKernelGGL(grad_reduce_flat_kernel, dim3((P + 255) / 256), dim3(256), 0, st, part, nblocks, P, grad,
+                           accumulate);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(grad_reduce_kernel, dim3((P + 7) / 8), dim3(256), 0, st, part, nblocks, P, grad, accumulate);
     return hipGetLastError();
 }
