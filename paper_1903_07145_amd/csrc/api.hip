@@ -512,18 +512,22 @@ static size_t plan_min(const Plan& pl, int64_t npix) {
 static size_t plan_full(const Plan& pl, int64_t npix) { return pl.end_fixed + 4 * 256 + (size_t)npix * pl.ck_per_pixel; }
 
 // Path streams or the per-lane state machine?  Returns the pixels per batch of
-// streams that fit into `bytes` of scratch, 0 for the state machine.  Streams
-// are faster at every size; the state machine runs what they do not provide
-// (path hashes, vertex records, the proposal network at every vertex), and
-// passes whose scratch holds neither all paths nor a batch of 2^19, where the
-// batches' launches would cost more than they save.  Few large batches: the
+// streams that fit into `bytes` of scratch, 0 for the state machine, which runs
+// what streams do not provide (path hashes, vertex records, the proposal network
+// at every vertex), passes of one path, and passes whose scratch holds neither
+// all paths nor a batch of 2^19, where the batches' launches would cost more than
+// they save.  One path has no company to gain from and pays for 2 D + 4 launches:
+// render of one path of the Cornell box 47 us by the state machine, 53 / 82 us by
+// streams at depth 1 / 7 (room 57-73, 63-103); with 2 to 12 paths it depends on
+// how early they end (0.5 to 1.7 times the state machine's time up to depth 7,
+// 0.9 on average), from 16 paths streams win.  Few large batches: the
 // apartment's step of 39 M paths takes 108 / 102 / 100 / 97 ms in batches of at
 // most 4 / 8 / 16 / 40 M.
 constexpr int64_t kStreamMaxPaths = 40 << 20;
 static int64_t stream_batch(const ipt_scene_s* s, const ipt_render_opts* o, int64_t npix, size_t bytes) {
     const int64_t npaths = npix * o->spp;
     const int gk = guide_kind(o);
-    if (gk == 1 || gk == 2 || o->debug_path_hash || o->debug_vertices) return 0;
+    if (npaths < 2 || gk == 1 || gk == 2 || o->debug_path_hash || o->debug_vertices) return 0;
     const size_t fixed = stream_fixed_bytes(s->num_cu);
     if (bytes <= fixed) return 0;
     const int64_t room = std::min<int64_t>((int64_t)((bytes - fixed) / kStreamPathBytes), kStreamMaxPaths);

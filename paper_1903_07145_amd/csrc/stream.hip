@@ -18,9 +18,9 @@
 // 90.2 ms, office floor render 19.8 -> 19.6).
 //
 // Measured, state machine -> streams: room step 17.4 -> 9.6 ms, apartment 132.6 ->
-// 95.8 ms, and the passes of 4096 to 524288 paths 1.3-4 times faster, so there is
-// no size at which the state machine is chosen; it serves the debug outputs, the
-// proposal network evaluated per vertex and calls with little workspace.
+// 95.8 ms, and the passes of 4096 to 524288 paths 1.3-4 times faster.  The state
+// machine serves single paths, the debug outputs, the proposal network evaluated
+// per vertex and calls with little workspace (stream_batch in api.hip).
 //
 // Lists are split over 8 groups, one per XCD (blocks b mod 8): with one list
 // for all, the appends' and chunk counters' atomics on one address took longer
