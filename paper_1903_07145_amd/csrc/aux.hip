@@ -23,10 +23,27 @@ hipError_t launch_zero_u32(unsigned* p, int n, hipStream_t st) {
 // proportional to the current emission of each object in a Fenwick tree
 // (Appendix E).  Here every call rebuilds the inclusive prefix sums of
 // weight_j = area_j * max(lum(e_k), 1e-3 * max lum) over emitter triangles
-// (area only if every emission is zero) with one block: each of the 1024
-// threads scans a contiguous run, the run totals are scanned in LDS, and the
-// runs are rescanned with their offsets.
+// (area only if every emission is zero).
 // ---------------------------------------------------------------------------
+// Weight of light j: one rounding per operation, so that a sum of weights adds the
+// rounded products wherever the compiler places them.
+struct LightWeight {
+    const int4* lights;
+    const float* e;       // emissions
+    float maxl;
+    __device__ float operator()(int64_t j) const {
+#pragma clang fp contract(off)
+        const int4 L = lights[j];
+        const float area = __int_as_float(L.z);
+        if (!(maxl > 0.0f)) return area;
+        const float* x = e + 3 * L.y;
+        const float l = (x[0] + x[1] + x[2]) * (1.0f / 3.0f);
+        return area * fmaxf(l, 1e-3f * maxl);
+    }
+};
+
+// The table by one block: each of the 1024 threads scans a contiguous run, the run
+// totals are scanned in LDS, and the runs are rescanned with their offsets.
 __global__ __launch_bounds__(1024) void light_cdf_kernel(const int4* lights, int nlt, int S, int E, int nm,
                                                          const float* sp, float* cdf) {
     __shared__ float part[1024];
@@ -44,14 +61,7 @@ __global__ __launch_bounds__(1024) void light_cdf_kernel(const int4* lights, int
     const float maxl = maxl_sh;
     const int per = (nlt + 1023) / 1024;
     const int b = tid * per, e_ = min(nlt, b + per);
-    auto weight = [&](int j) {
-        int4 L = lights[j];
-        float area = __int_as_float(L.z);
-        if (!(maxl > 0.0f)) return area;
-        const float* e = sp + nm * S + 3 * L.y;
-        float l = (e[0] + e[1] + e[2]) * (1.0f / 3.0f);
-        return area * fmaxf(l, 1e-3f * maxl);
-    };
+    const LightWeight weight{lights, sp + nm * S, maxl};
     float s = 0.0f;
     for (int j = b; j < e_; ++j) s += weight(j);
     part[tid] = s;
@@ -76,24 +86,10 @@ __global__ __launch_bounds__(1024) void light_cdf_kernel(const int4* lights, int
 // The same table for many lights (more than kManyLights) by three kernels (500,582
 // lights: 3455 -> 26 us; one block waits for its strided loads): a block per run computes the
 // run's weights with all its threads and adds them with one, in the same order;
-// one block scans the run totals; the blocks write their runs.  Same sums in the
-// same order as above, so the same table bit for bit.
+// one block scans the run totals; the blocks write their runs.  The same weights
+// (LightWeight), summed in the same order as above: the same table bit for bit.
 constexpr int kRuns = 1024;       // runs of the table
 constexpr int kRunTile = 2048;    // lights of a run held in LDS at a time
-
-struct LightWeight {
-    const int4* lights;
-    const float* e;       // emissions
-    float maxl;
-    __device__ float operator()(int64_t j) const {
-        const int4 L = lights[j];
-        const float area = __int_as_float(L.z);
-        if (!(maxl > 0.0f)) return area;
-        const float* x = e + 3 * L.y;
-        const float l = (x[0] + x[1] + x[2]) * (1.0f / 3.0f);
-        return area * fmaxf(l, 1e-3f * maxl);
-    }
-};
 
 // Largest emission luminance, over the block.
 __device__ float block_max_lum(const float* e, int E) {
