@@ -519,10 +519,12 @@ static size_t plan_full(const Plan& pl, int64_t npix) { return pl.end_fixed + 4 
 // they save.  One path has no company to gain from and pays for 2 D + 4 launches:
 // render of one path of the Cornell box 47 us by the state machine, 53 / 82 us by
 // streams at depth 1 / 7 (room 57-73, 63-103); with 2 to 12 paths it depends on
-// how early they end (0.5 to 1.7 times the state machine's time up to depth 7,
+// how early they end (0.5 to 1.8 times the state machine's time up to depth 7,
 // 0.9 on average), from 16 paths streams win.  Few large batches: the
 // apartment's step of 39 M paths takes 108 / 102 / 100 / 97 ms in batches of at
-// most 4 / 8 / 16 / 40 M.
+// most 4 / 8 / 16 / 40 M.  The bound is one of memory: the lists of 40 Mi paths take
+// 9.4 GB, next to the vertex records (15 GB for that step), and a doubling of the
+// batch saves 2% at that size.
 constexpr int64_t kStreamMaxPaths = 40 << 20;
 static int64_t stream_batch(const ipt_scene_s* s, const ipt_render_opts* o, int64_t npix, size_t bytes) {
     const int64_t npaths = npix * o->spp;

@@ -8,7 +8,9 @@
 //   row 0: origin x, y, z (float); biased exponents e_x, e_y, e_z (bytes 0-2)
 //   row 1: x lo, x hi, y lo, y hi of the four children (one byte per child)
 //   row 2: z lo, z hi; the cell sizes 2^(e + 24) of x and y (the upper 16 bits
-//          of a float each, y's in the low half) and of z (float)
+//          of a float each, y's in the low half) and of z (float).  They are normal
+//          floats: e >= -126, and e <= 34 since the scene build refuses coordinates
+//          beyond 1e12
 //   row 3: the four child references (as the float layout)
 // A plane decodes to origin + q 2^e.  Every decoded box contains its child's
 // float box widened by delta = 2^-20 of the node's largest extent on every

@@ -292,7 +292,9 @@ constexpr int kTS = 72;
 // Four waves (64 records) per block: forward, loss, backward.  A wave owns 16 of
 // the records (rows) in the products along the layers and 16 of the inputs in
 // the weight gradients, so the waves share nothing but the activations; the
-// products' operands and order are those of one wave doing all.  The serial
+// products' operands and order are those of one wave doing all.  (Two runs differ by
+// up to 2e-5 of the gradient's norm all the same: the sum of the weights is added by
+// atomics, and its last bit moves derivatives across a rounding to bfloat16.)  The serial
 // chain of layers, not arithmetic, bounds a block: 16384 records (one block per
 // CU) took 158 us with one wave per block, 42 us with four.
 __global__ __launch_bounds__(256) void guide_train_kernel(TrainArgs t) {

@@ -3,11 +3,12 @@
 // same boxes, triangles and tie rule as the traversal of path_dev.h, so the
 // same hits; only the order of visits can differ (children at equal distance).
 //
-// Bound by VALU issue (73-79% of its cycles busy) with 4-cycle min/max, select
-// and byte-permute instructions (fma, add, mul and bit operations take 2), then
-// by the latency of the node loads.  4.9 M camera rays of the apartment: 5.0 ->
-// 7.7 G rays/s, 60 instead of 89 wave instructions per ray, 55% instead of 41% of
-// the lanes active.
+// Bound by VALU issue with 4-cycle min/max, select and byte-permute instructions
+// (fma, add, mul and bit operations take 2), then by the address unit and the
+// latency of the node loads.  Rays of the apartment's path passes: VALU busy in
+// 87-89% of the cycles, 59-60% of the lanes active, 0.81 accesses per clock and CU.
+// A batch of 4.9 M camera rays: 75-82% and 52% (41% before), 63 instead of 89 wave
+// instructions per ray, 5.0 -> 7.7 G rays/s.
 #pragma once
 #include "path_dev.h"
 
@@ -113,7 +114,7 @@ __device__ __forceinline__ bool tri_isect_axes(float ox, float oy, float oz, flo
 // Traces rays [0, n) of a source: src.load(i, o, d, tmax, skip0, skip1, any)
 // fetches a ray (any: stop at the first hit below tmax; skip0 and skip1 are
 // leaf triangles to ignore), src.store(i, any, hit) takes its result.
-// // nwaves waves run it, this one as number `wave`; each takes chunks of
+// nwaves waves run it, this one as number `wave`; each takes chunks of
 // consecutive rays: the next one of the counter `work` (zero at the start).
 template <class SRC>
 __device__ __forceinline__ void trace_stream(const SceneDev& sc, float tmin, const SRC& src, unsigned n, int* lds_stack,

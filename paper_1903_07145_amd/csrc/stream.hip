@@ -245,7 +245,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kRayBloc
 }
 
 // Shading of vertex k for every closest-hit ray of the list.  Bound by memory
-// latency (78% of the lanes active; L1 waits 64-71% of the cycles): 7.3 and 12 ms of
+// latency (78-80% of the lanes active; L1 waits 64-71% of the cycles): 7.3 and 12 ms of
 // the apartment step's two passes.  No spills (98-157 VGPRs), unlike the state
 // machine's 41-51; a forced fourth or fifth wave per SIMD changed nothing (97.0 ms)
 // or spilled (102.2 ms).
@@ -259,7 +259,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     const SceneDev& sc = a.sc;
     const float* cdf = lds.lights_in_lds ? lds.cdf : a.cdf;
     const int4* lights = lds.lights_in_lds ? lds.lights : sc.lights;
-    // the rounding of e1 u + e2 v in the state machine's variants
+    // The rounding of e1 u + e2 v in the state machine's variants, as the compiler
+    // contracts it there; no rule predicts it.  test_gpu_streams compares every
+    // variant bit for bit and has to be run after a change of that code or of the
+    // compiler.
     constexpr int UV = MAT == 0 && (PG == 0 || GUIDE == 3) ? 2 : 1;
     const int k = t.k, D = a.D;
     const int in = (k - 1) & 1, out = k & 1;
