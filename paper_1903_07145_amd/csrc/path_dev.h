@@ -547,6 +547,14 @@ struct NeeS {
     bool shoot;   // geometric tests passed: a shadow ray is needed
 };
 
+// How the forward passes round e1 u + e2 v in nee_setup (its UV), by proposal,
+// parameter storage and material: what the state machine's variants were first
+// compiled to, fixed here so that streams and state machine give the same bits
+// whatever a compiler contracts.
+__host__ __device__ constexpr int uv_rounding(int guide, int pg, int mat) {
+    return guide == 1 || guide == 2 ? 0 : (mat == 0 && (pg == 0 || guide == 3) ? 2 : 1);
+}
+
 // Pick an emitter triangle from the table and a uniform point on it.  UV: how
 // e1 u + e2 v is rounded: 0 as the compiler contracts it in this place, 1 with
 // the first, 2 with the second product fused into the sum.

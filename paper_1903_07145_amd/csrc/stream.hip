@@ -259,11 +259,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     const SceneDev& sc = a.sc;
     const float* cdf = lds.lights_in_lds ? lds.cdf : a.cdf;
     const int4* lights = lds.lights_in_lds ? lds.lights : sc.lights;
-    // The rounding of e1 u + e2 v in the state machine's variants, as the compiler
-    // contracts it there; no rule predicts it.  test_gpu_streams compares every
-    // variant bit for bit and has to be run after a change of that code or of the
-    // compiler.
-    constexpr int UV = MAT == 0 && (PG == 0 || GUIDE == 3) ? 2 : 1;
+    constexpr int UV = uv_rounding(GUIDE, PG, MAT);
     const int k = t.k, D = a.D;
     const int in = (k - 1) & 1, out = k & 1;
     const unsigned group = blockIdx.x % kStreamGroups, first = group * t.cap;

@@ -95,6 +95,7 @@ __attribute__((amdgpu_waves_per_eu((GUIDE == 1 || GUIDE == 2) ? IPT_WAVES_PER_EU
     const int4* lights = lds.lights_in_lds ? lds.lights : sc.lights;
     const int lane = threadIdx.x & 63;
     const int64_t npix_img = (int64_t)a.V * a.W * a.H;
+    constexpr int UV = uv_rounding(GUIDE, PG, MAT);
     const int D = a.D;
     Work wk{0u, 0u, 0u, 0u, 0u};
     uint32_t npaths = 0;
@@ -335,7 +336,7 @@ __attribute__((amdgpu_waves_per_eu((GUIDE == 1 || GUIDE == 2) ? IPT_WAVES_PER_EU
                 n.lj = 0;
                 const bool do_nee = a.mis != 0 && sc.nlt > 0;
                 if (do_nee) {
-                    n = nee_setup(sc, cdf, lights, g, u);
+                    n = nee_setup<UV>(sc, cdf, lights, g, u);
                     ev |= (uint32_t)n.lj << 8;
                 }
                 const ContDir cd = cont_direction_cached(a, g, ms, u, mix);
@@ -349,7 +350,7 @@ __attribute__((amdgpu_waves_per_eu((GUIDE == 1 || GUIDE == 2) ? IPT_WAVES_PER_EU
                 used_guide = cd.guide;
             } else {
                 if (a.mis != 0 && sc.nlt > 0) {
-                    NeeS n = nee_setup(sc, cdf, lights, g, u);
+                    NeeS n = nee_setup<UV>(sc, cdf, lights, g, u);
                     ev |= (uint32_t)n.lj << 8;
                     if (n.shoot) {
                         if (GUIDE && mix)
