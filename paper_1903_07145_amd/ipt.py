@@ -198,7 +198,7 @@ def render_opts(seed=0, stream_tag=1, iteration=0, spp=4, max_depth=3, rr_depth=
     o.path_mask = None if path_mask is None else path_mask.data_ptr()
     o.debug_path_radiance = None if debug_path_radiance is None else debug_path_radiance.data_ptr()
     o.debug_vertices = None if debug_vertices is None else debug_vertices.data_ptr()
-    o._keep = (pixel_list, debug_path_hash, path_mask, debug_path_radiance, debug_vertices)
+    o._keep = (pixel_list, guide, debug_path_hash, path_mask, debug_path_radiance, debug_vertices)
     return o
 
 
